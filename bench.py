@@ -304,8 +304,12 @@ def main():
     del stream
 
     wc_flops, single_flops, prop_bytes = algorithmic_counts(N, nr, nR)
-    if args.precision == "separable":
-        # the contraction through K products: N(N+1)/2 pairs x (n_r + n_R) x K complex x real multiply-adds
+    # the contraction through K products (all of it in every form where W_c is such a sum to its rounding; the mixed
+    # form's FP32 pass else has whole blocks of 16 beside it): N(N+1)/2 pairs x (n_r + n_R) x K complex x real
+    # multiply-adds, in FP64
+    products = rank > 0 and (args.precision != "mixed" or rank % 16 != 0)
+    peak = PEAK["fp64"] if products else PEAK[args.precision]
+    if products:
         wc_flops = 2.0 * N * (N + 1) * (nr + nR) * rank
     n_wc, ms_wc = kt["wc_contract"]
     wc_avg_s = ms_wc / 1e3 / n_wc
@@ -313,15 +317,15 @@ def main():
     n_zg, ms_zg = kt["zgemm"]
     # S/H build: the contraction plus the single-species integrals.  From 1024
     # padded trajectories the step runs the integrals on the second stream
-    # beside the contraction where that stream has room: FP64 without the
+    # beside a dense contraction where that stream has room: FP64 without the
     # explicit inverses of S + eps I (used for a power-of-two padded count), or
-    # a dense contraction with n_r n_R >= 256 Np.  The build then spans the
+    # n_r n_R >= 256 Np.  The build then spans the
     # longer of the two; otherwise they run one after the other.
     Np = (N + 63) // 64 * 64
-    dense = args.precision != "separable"
+    dense = not products
     sinv = Np >= 1024 and (Np & (Np - 1)) == 0
     roomy = dense and nr * nR >= 256 * Np
-    concurrent = Np >= 1024 and ((args.precision == "fp64" and not sinv) or roomy)
+    concurrent = Np >= 1024 and dense and ((args.precision == "fp64" and not sinv) or roomy)
     build_ms = max(ms_wc, ms_zg) if concurrent else ms_wc + ms_zg
     build_tflops = (wc_flops + single_flops) / (build_ms / 1e3 / n_wc) / 1e12
     build_tflops_summed = (wc_flops + single_flops) / ((ms_wc + ms_zg) / 1e3 / n_wc) / 1e12
@@ -346,8 +350,8 @@ def main():
                    "n_r": nr, "n_R": nR,
                    "dt": wl.dt, "precision": args.precision, "propagator": args.propagator, "contraction_rank": rank,
                    "timing": "kernel-by-kernel with HIP events"},
-        "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK[args.precision], "unit": "TFLOP/s",
-                     "frac": achieved / PEAK[args.precision],
+        "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
+                     "frac": achieved / peak,
                      "traffic": measured_traffic(args.workload, args.precision),
                      "kernel": "wc_contract", "flops_per_launch": wc_flops, "avg_launch_ms": wc_avg_s * 1e3},
         "sh_build_tflops": build_tflops,

@@ -69,10 +69,14 @@ typedef enum {
 } icwf_model;
 
 typedef enum {
-    ICWF_PREC_FP64 = 0,  /* every step in FP64                                        */
-    ICWF_PREC_MIXED = 1, /* Eq. 9b's two-body contraction in FP32 on the matrix cores,
-                            accumulated in FP32 inside each R tile and in FP64 across
-                            tiles; everything else FP64                              */
+    ICWF_PREC_FP64 = 0,  /* every step in FP64; Eq. 9b through the sum of products of
+                            ICWF_PREC_SEPARABLE where one exists and is the cheaper,
+                            else over the W_c table                                  */
+    ICWF_PREC_MIXED = 1, /* as ICWF_PREC_FP64 where such a sum costs less than the
+                            following; else Eq. 9b's two-body contraction of what a
+                            short sum leaves in FP32 on the matrix cores, accumulated
+                            in FP32 inside each R tile and in FP64 across tiles;
+                            everything else FP64                                     */
     ICWF_PREC_SEPARABLE = 2 /* FP64 throughout, Eq. 9b's two-body sum taken through a
                             sum of products W_c(r_i, R_j) = sum_k u_k(r_i) v_k(R_j)
                             of at most 64 terms, found at creation by cross
@@ -193,8 +197,8 @@ icwf_status icwf_step(icwf_sim *sim, int32_t n_steps);
  * stream, at the same step parity, each one that steps on a single stream
  * without the explicit inverses (padded N < 1024) and without per-kernel
  * timing, and all alike in N, grids, boxes, masses, dt, eps, model kind,
- * precision (and contraction rank in blocks of 16), propagator, trajectory
- * integrator and n_bo; model parameters may differ.  A handle stopped by an
+ * precision (and, for a separable or mixed one, its rank in blocks of 16),
+ * propagator, trajectory integrator and n_bo; model parameters may differ.  A handle stopped by an
  * earlier error is ICWF_ESTATE.  Errors raised on the device stop only the
  * simulation that raised them (reported by its next synchronising call).
  * The handles of sims[] are caller-owned; the first one's workspace holds the
@@ -237,9 +241,9 @@ icwf_status icwf_kernel_time(icwf_sim *sim, const char *name, int64_t *launches,
                              double *total_ms);
 
 /* Number of terms K of the sum of products W_c = sum_k u_k v_k the handle's
- * two-body contraction uses (Eq. 9b): the rank-K FP64 part of
- * ICWF_PREC_MIXED, the whole contraction of ICWF_PREC_SEPARABLE, 0 for
- * ICWF_PREC_FP64.  *rank: caller-owned host int32.  ICWF_EINVAL on NULL. */
+ * two-body contraction uses (Eq. 9b): the whole contraction, or the rank-K
+ * FP64 part beside the FP32 pass of ICWF_PREC_MIXED; 0 where the W_c table is
+ * summed.  *rank: caller-owned host int32.  ICWF_EINVAL on NULL. */
 icwf_status icwf_contraction_rank(const icwf_sim *sim, int32_t *rank);
 
 /* Release the handle (not the workspace).  NULL is ignored. */

@@ -74,6 +74,7 @@ Bufs carve(const icwf_config &c, char *base, size_t *total) {
     b.psi1_f32 = L.take<float2>(mixed ? Np * nr : 1);
     b.lr_u = L.take<double>(icwf::kLowRankMax * nr);
     b.lr_v = L.take<double>(icwf::kLowRankMax * nR);
+    b.lr_pad = L.take<int32_t>(1);
     b.sinc_r = L.take<double>(Np * nr);
     b.dsinc_r = L.take<double>(Np * nr);
     b.sinc_R = L.take<double>(Np * nR);
@@ -174,25 +175,36 @@ double h_wc(const icwf_config &c, double r, double R) {
 // remaining entry as pivot, so the residual's maximum never grows.)
 int cross_approximation(std::vector<double> &W, int n, int m, double tol, int kmax, std::vector<double> &U,
                         std::vector<double> &V) {
-    double wmax = 0.0;
-    for (double w : W) wmax = std::max(wmax, std::fabs(w));
+    // largest |entry| of a row (eight running maxima: no serial chain)
+    auto row_max = [m](const double *w) {
+        double mx[8] = {};
+        for (int j = 0; j < m; j += 8)               // m is a power of two >= 32
+            for (int l = 0; l < 8; ++l) {
+                const double x = std::fabs(w[j + l]);
+                mx[l] = x > mx[l] ? x : mx[l];
+            }
+        return *std::max_element(mx, mx + 8);
+    };
+    std::vector<double> rmax(n);
+    for (int i = 0; i < n; ++i) rmax[i] = row_max(&W[(size_t)i * m]);
+    const double wmax = *std::max_element(rmax.begin(), rmax.end());
+    std::vector<double> u(n), v(m);
     int k = 0;
     for (; k < kmax; ++k) {
-        size_t piv = 0;
-        double best = -1.0;
-        for (size_t e = 0; e < W.size(); ++e)
-            if (std::fabs(W[e]) > best) {
-                best = std::fabs(W[e]);
-                piv = e;
-            }
+        const int pi = (int)(std::max_element(rmax.begin(), rmax.end()) - rmax.begin());
+        const double best = rmax[pi];
         if (best <= tol * wmax || best == 0.0) break;
-        const int pi = (int)(piv / m), pj = (int)(piv % m);
-        const double p = W[piv];
-        std::vector<double> u(n), v(m);
+        const double *prow = &W[(size_t)pi * m];
+        int pj = 0;
+        while (std::fabs(prow[pj]) != best) ++pj;
+        const double p = prow[pj];
         for (int i = 0; i < n; ++i) u[i] = W[(size_t)i * m + pj];
-        for (int j = 0; j < m; ++j) v[j] = W[(size_t)pi * m + j] / p;
-        for (int i = 0; i < n; ++i)
-            for (int j = 0; j < m; ++j) W[(size_t)i * m + j] -= u[i] * v[j];
+        for (int j = 0; j < m; ++j) v[j] = prow[j] / p;
+        for (int i = 0; i < n; ++i) {
+            double *w = &W[(size_t)i * m];
+            for (int j = 0; j < m; ++j) w[j] -= u[i] * v[j];
+            rmax[i] = row_max(w);
+        }
         U.insert(U.end(), u.begin(), u.end());
         V.insert(V.end(), v.begin(), v.end());
     }
@@ -202,7 +214,8 @@ int cross_approximation(std::vector<double> &W, int n, int m, double tol, int km
 // Largest relative residual the mixed form leaves to FP32 (more terms are
 // taken where they fill the FP64 part's last block of 16).
 constexpr double kMixedSplitTol = 1e-4;
-// Residual the separable form accepts: a few roundings of the table itself.
+// Residual a sum of products that stands for the whole table may leave: a few
+// roundings of the table itself.
 constexpr double kSeparableTol = 4.0 * 2.220446049250313e-16;
 
 struct Timer {
@@ -225,6 +238,7 @@ struct icwf_sim {
     Dims d{};
     Bufs b{};
     int Np = 0;
+    int key_blocks = 0, key_residual = 0;     // of the sum of products the precision form asks for (batch_key)
     hipStream_t stream = nullptr;
     hipStream_t capture_stream = nullptr;
     hipStream_t side_stream = nullptr;        // the S assembly and the factorisations, beside the contraction
@@ -283,10 +297,10 @@ void timed(icwf_sim *s, const char *name, hipStream_t st, F fn) {
 // One step on stream st.  The two-body contraction needs neither the
 // single-species integrals nor the Cholesky factorisations, which need only S:
 // from kOverlapMinN padded trajectories on, the step forks, the side stream
-// assembles S and factors S + eps I (in the FP64 form, where the contraction
-// is the longest branch, after computing the single-species integrals
-// itself) while st contracts W_c (in the separable form, whose contraction is
-// short, followed by the coupling integrals); st then waits for the side
+// assembles S and factors S + eps I (beside a dense FP64 contraction without
+// the explicit inverses, the longest branch, after computing the
+// single-species integrals itself) while st contracts W_c (through products,
+// a short contraction, followed by the coupling integrals); st then waits for the side
 // stream, assembles K and runs the RK4 stages.  The persistent contraction leaves CU slots free for the side
 // stream's latency-bound kernels.  Smaller simulations (whose contraction
 // does not fill the GPU, and which a server runs many at a time) stay on one
@@ -310,13 +324,13 @@ void enqueue_step(icwf_sim *s, const Dims &d, int parity, hipStream_t st, hipStr
     // pair, n_r n_R, is at least 256 N (the factorisations and inversions, N^3,
     // then take a small part of its time); otherwise they stay on st, ahead of
     // the fork
-    const bool roomy = d.prec != ICWF_PREC_SEPARABLE && (size_t)d.nr * d.nR >= 256 * (size_t)s->Np;
-    const hipStream_t ss = fork && ((d.prec == ICWF_PREC_FP64 && !d.sinv) || roomy) ? side : st;
-    // the separable form's contraction is the short branch: ahead of the fork
+    const bool roomy = !d.products && (size_t)d.nr * d.nR >= 256 * (size_t)s->Np;
+    const hipStream_t ss = fork && ((d.prec == ICWF_PREC_FP64 && !d.products && !d.sinv) || roomy) ? side : st;
+    // a contraction through products is the short branch: ahead of the fork
     // only the overlaps (all that S needs), the coupling integrals (needed by
     // K only) on st after the contraction, while the factorisation stream
     // still runs
-    const bool late_couplings = fork && ss == st && d.prec == ICWF_PREC_SEPARABLE;
+    const bool late_couplings = fork && ss == st && d.products;
     auto single_species = [&](hipStream_t q, int parts) {
         // with Heun trajectories the integrals at x_k+1 wait for the corrector
         timed(s, "zgemm", q, [&] {
@@ -330,7 +344,7 @@ void enqueue_step(icwf_sim *s, const Dims &d, int parity, hipStream_t st, hipStr
         (void)hipStreamWaitEvent(side, s->ev_fork, 0);
     }
     if (ss != st) single_species(ss, icwf::kSingleAll);
-    // with the factorisations as the longer branch (the separable form), the
+    // with the factorisations as the longer branch (through products), the
     // explicit inverses wait for the join and then take the whole GPU on st
     // instead of stretching the second stream further
     const bool late_inverses = late_couplings && d.sinv;
@@ -415,7 +429,7 @@ bool batch_key(const icwf_sim *s, std::string *key) {
         return std::to_string(u);
     };
     std::string k;
-    for (int v : {d.N, d.nr, d.nR, d.n_bo, d.prec, (d.lr_rank + 15) / 16, d.fp32_residual, d.propagator, d.traj,
+    for (int v : {d.N, d.nr, d.nR, d.n_bo, d.prec, s->key_blocks, s->key_residual, d.propagator, d.traj,
                   d.wc_grid, d.prop_grid[0], d.prop_grid[1], (int)d.mp.kind, icwf::propagate_tiny_phase(d) ? 1 : 0})
         k += std::to_string(v) + ",";
     for (double v : {d.r_min, d.hr, d.R_min, d.hR, d.m_r, d.m_R, d.dt, d.eps}) k += bits(v) + ",";
@@ -532,7 +546,6 @@ icwf_status icwf_create(const icwf_config *cfg, const double *r0, const double *
         }
     if (!finite(vr.data(), nr) || !finite(vR.data(), nR) || !finite(wc.data(), wc.size()))
         return cleanup_fail(ICWF_ENONFINITE, "the model is singular on the grid");
-    // mixed form: W_c = (rank-K part, FP64) + (residual, FP32 matrix cores)
     std::vector<double> lr_u, lr_v;
     d.lr_rank = 0;
     int ncu = 0;
@@ -545,49 +558,86 @@ icwf_status icwf_create(const icwf_config *cfg, const double *r0, const double *
         d.prop_grid[0] = icwf::propagate_grid(nr, N, ncu);
         d.prop_grid[1] = icwf::propagate_grid(nR, N, ncu);
     }
+    auto maxabs = [](const std::vector<double> &v) {
+        double m = 0.0;
+        for (double x : v) m = std::max(m, std::fabs(x));
+        return m;
+    };
+    const double wmax = maxabs(wc);
+    std::vector<double> res = wc;
+    double rmax = wmax;
+    // terms of the approximation up to kmax, or until the residual is at the table's own rounding
+    auto extend = [&](double tol, int kmax) {
+        if (kmax <= d.lr_rank || rmax <= tol * wmax) return;
+        d.lr_rank += cross_approximation(res, nr, nR, tol * wmax / rmax, kmax - d.lr_rank, lr_u, lr_v);
+        rmax = maxabs(res);
+    };
+    auto exact = [&] { return d.lr_rank > 0 && rmax <= kSeparableTol * wmax; };
+    auto blocks = [](int rank) { return (rank + 15) / 16; };
     if (cfg->precision == ICWF_PREC_MIXED) {
-        std::vector<double> res = wc;
-        d.lr_rank = cross_approximation(res, nr, nR, kMixedSplitTol, icwf::kLowRankMax, lr_u, lr_v);
-        auto maxabs = [](const std::vector<double> &v) {
-            double m = 0.0;
-            for (double x : v) m = std::max(m, std::fabs(x));
-            return m;
-        };
-        const double wmax = maxabs(wc);
-        double rmax = maxabs(res);
+        // W_c = (rank-K part, FP64) + (residual, FP32 matrix cores)
+        extend(kMixedSplitTol, icwf::kLowRankMax);
         // the FP64 part runs in blocks of 16 terms, so terms up to the next
         // multiple of 16 cost nothing: take them (down to the table's rounding),
         // which leaves a smaller residual, and so a smaller FP32 error, to the
         // matrix-core pass
-        const int fill = std::min(icwf::kLowRankMax, (d.lr_rank + 15) / 16 * 16);
-        if (d.lr_rank > 0 && fill > d.lr_rank && rmax > kSeparableTol * wmax) {
-            d.lr_rank += cross_approximation(res, nr, nR, kSeparableTol * wmax / rmax, fill - d.lr_rank, lr_u, lr_v);
-            rmax = maxabs(res);
-        }
-        for (size_t e = 0; e < res.size(); ++e) wc32[e] = static_cast<float>(res[e]);
+        if (d.lr_rank > 0) extend(kSeparableTol, std::min(icwf::kLowRankMax, 16 * blocks(d.lr_rank)));
         // a residual at the table's own rounding level (an exactly separable
         // coupling, such as the cavity's lambda q x) leaves the FP32 pass
         // nothing to add: the FP64 rank-K part is then the whole contraction
-        d.fp32_residual = !(d.lr_rank > 0 && rmax <= kSeparableTol * wmax);
+        d.fp32_residual = !exact();
     } else if (cfg->precision == ICWF_PREC_SEPARABLE) {
-        std::vector<double> res = wc;
-        d.lr_rank = cross_approximation(res, nr, nR, kSeparableTol, icwf::kLowRankMax, lr_u, lr_v);
-        double wmax = 0.0, rmax = 0.0;
-        for (size_t e = 0; e < wc.size(); ++e) {
-            wmax = std::max(wmax, std::fabs(wc[e]));
-            rmax = std::max(rmax, std::fabs(res[e]));
-        }
+        extend(kSeparableTol, icwf::kLowRankMax);
         if (rmax > kSeparableTol * wmax)
             return cleanup_fail(ICWF_EINVAL, "W_c is not a sum of at most 64 products to FP64 rounding; use the FP64 form");
-        // a contraction through few products is the short branch of a forked
-        // step where (n_r + n_R) K < 32 N (K in blocks of 16; N = 1024 on 512 x
-        // 256, K = 28: 1.2 ms beside 1.9 ms of factorisations; N = 4096 on 4096
-        // x 512, K = 41: 88 ms beside 49 ms): it then takes one work-group per
-        // CU and leaves the other slots to the factorisation stream
-        const size_t kp = (size_t)(d.lr_rank + 15) / 16 * 16;
-        if (icwf::padded(N) >= kOverlapMinN && (size_t)(nr + nR) * kp < 32 * (size_t)icwf::padded(N))
-            d.wc_grid = ncu;
     }
+    s->key_blocks = blocks(d.lr_rank);
+    s->key_residual = d.fp32_residual;
+    d.products = cfg->precision == ICWF_PREC_SEPARABLE || (cfg->precision == ICWF_PREC_MIXED && !d.fp32_residual);
+    if (!d.products) {
+        // the dense pass over the table gives way to a sum of products that is
+        // the table to its rounding where that sum is the cheaper one: K (in
+        // blocks of 16) products over n_r + n_R points instead of n_r n_R
+        // points per pair, on the same matrix cores; in the mixed form the
+        // terms beyond the rank part, in FP64, instead of the FP32 pass over
+        // the residual at twice the rate
+        const size_t sum = (size_t)(nr + nR), dense = (size_t)nr * nR;
+        const bool mixed = cfg->precision == ICWF_PREC_MIXED && d.fp32_residual;
+        const int done = 16 * blocks(d.lr_rank), kept = d.lr_rank;
+        const int kmax = (int)std::min<size_t>(icwf::kLowRankMax, done + (mixed ? dense / 2 : dense) / sum / 16 * 16);
+        std::vector<double> keep = mixed ? res : std::vector<double>();
+        extend(kSeparableTol, kmax);
+        if (exact()) {
+            d.products = 1;
+            d.fp32_residual = 0;
+        } else {                                     // no such sum: as the form has it
+            d.lr_rank = kept;
+            lr_u.resize((size_t)kept * nr);
+            lr_v.resize((size_t)kept * nR);
+            res.swap(keep);
+        }
+    }
+    if (d.fp32_residual)
+        for (size_t e = 0; e < res.size(); ++e) wc32[e] = static_cast<float>(res[e]);
+    // a contraction through few products is the short branch of a forked
+    // step where (n_r + n_R) K < 32 N (K in blocks of 16): it then takes five
+    // work-groups per four CUs and leaves room to the factorisation stream
+    // (N = 1024 on 512 x 256, K = 28: 2.22 ms per step, 2.23 with one per CU,
+    // 2.38 with the 2 ncu - 64 of the longer contractions; N = 2048 cavity, K =
+    // 1: 8.46, 8.96 and 8.86; but N = 1500 on 1024 x 512, K = 29, on the other
+    // side of the line: 7.75, 8.29 and 7.23)
+    if (d.products && Np >= kOverlapMinN && (size_t)(nr + nR) * 16 * blocks(d.lr_rank) < 32 * (size_t)Np)
+        d.wc_grid = ncu + ncu / 4;
+    // rank factors in blocks of 16, laid out [block][n / 2][16][2] as the contraction's lanes read them
+    auto rank_blocks = [&](const std::vector<double> &f, int n) {
+        std::vector<double> out((size_t)(d.lr_rank + 15) / 16 * 16 * n, 0.0);
+        for (int k = 0; k < d.lr_rank; ++k)
+            for (int i = 0; i < n; ++i)
+                out[((size_t)(k / 16) * (n / 2) + i / 2) * 32 + (k % 16) * 2 + (i & 1)] = f[(size_t)k * n + i];
+        return out;
+    };
+    lr_u = rank_blocks(lr_u, nr);
+    lr_v = rank_blocks(lr_v, nR);
     auto fill_k = [&](std::vector<double2> &kin, std::vector<double2> &tw, int n, double h, double m) {
         for (int k = 0; k < n; ++k) {
             const int kk = (k <= n / 2) ? k : k - n;
@@ -628,6 +678,8 @@ icwf_status icwf_create(const icwf_config *cfg, const double *r0, const double *
     CREATE_HIP(hipMemcpyAsync(b.tw_R, tw_R.data(), sizeof(double2) * nR, hipMemcpyHostToDevice, st));
     CREATE_HIP(hipMemcpyAsync(b.wc64, wc.data(), sizeof(double) * wc.size(), hipMemcpyHostToDevice, st));
     CREATE_HIP(hipMemcpyAsync(b.wc32, wc32.data(), sizeof(float) * wc32.size(), hipMemcpyHostToDevice, st));
+    const int32_t lr_pad = 16 * blocks(d.lr_rank);
+    CREATE_HIP(hipMemcpyAsync(b.lr_pad, &lr_pad, sizeof(int32_t), hipMemcpyHostToDevice, st));
     if (d.lr_rank > 0) {
         CREATE_HIP(hipMemcpyAsync(b.lr_u, lr_u.data(), sizeof(double) * lr_u.size(), hipMemcpyHostToDevice, st));
         CREATE_HIP(hipMemcpyAsync(b.lr_v, lr_v.data(), sizeof(double) * lr_v.size(), hipMemcpyHostToDevice, st));
@@ -688,28 +740,13 @@ icwf_status icwf_step(icwf_sim *s, int32_t n_steps) {
     return ICWF_OK;
 }
 
-icwf_status icwf_step_batch(icwf_sim *const *sims, int32_t n_sims, int32_t n_steps) {
-    if (!sims || n_sims < 1 || n_sims > icwf::kMaxBatch || n_steps < 0)
-        return fail(nullptr, ICWF_EINVAL, "icwf_step_batch: need 1..64 simulations and n_steps >= 0");
+namespace {
+
+// n_steps steps of simulations that one launch per kernel advances together
+icwf_status step_group(const std::vector<icwf_sim *> &sims, int32_t n_steps) {
+    const int n_sims = (int)sims.size();
+    if (n_sims == 0) return ICWF_OK;
     icwf_sim *lead = sims[0];
-    if (!lead) return fail(nullptr, ICWF_EINVAL, "icwf_step_batch: NULL simulation");
-    std::string key;
-    if (!batch_key(lead, &key))
-        return fail(lead, ICWF_EINVAL, "icwf_step_batch: this simulation steps alone (padded N >= 1024, explicit "
-                                       "inverses or per-kernel timing)");
-    for (int k = 0; k < n_sims; ++k) {
-        icwf_sim *s = sims[k];
-        std::string kk;
-        if (!s) return fail(lead, ICWF_EINVAL, "icwf_step_batch: NULL simulation");
-        for (int q = 0; q < k; ++q)
-            if (sims[q] == s) return fail(lead, ICWF_EINVAL, "icwf_step_batch: a simulation appears twice");
-        if (s->status != ICWF_OK) return fail(s, ICWF_ESTATE, "the simulation stopped on an earlier error");
-        if (!batch_key(s, &kk) || kk != key)
-            return fail(lead, ICWF_EINVAL, "icwf_step_batch: the simulations differ in shape or parameters the "
-                                           "launches share");
-        if (s->stream != lead->stream) return fail(lead, ICWF_EINVAL, "icwf_step_batch: the simulations must share a stream");
-        if (s->parity != lead->parity) return fail(lead, ICWF_EINVAL, "icwf_step_batch: the simulations are at steps of different parity");
-    }
     if (n_sims == 1) return icwf_step(lead, n_steps);
     // the batch table: each simulation's workspace relative to the lead's (the
     // workspace starts with the flags), written by a kernel whose arguments
@@ -743,6 +780,44 @@ icwf_status icwf_step_batch(icwf_sim *const *sims, int32_t n_sims, int32_t n_ste
             sims[q]->parity ^= 1;
             sims[q]->step += 1;
             sims[q]->t += sims[q]->d.dt;
+        }
+    }
+    return ICWF_OK;
+}
+
+}  // namespace
+
+icwf_status icwf_step_batch(icwf_sim *const *sims, int32_t n_sims, int32_t n_steps) {
+    if (!sims || n_sims < 1 || n_sims > icwf::kMaxBatch || n_steps < 0)
+        return fail(nullptr, ICWF_EINVAL, "icwf_step_batch: need 1..64 simulations and n_steps >= 0");
+    icwf_sim *lead = sims[0];
+    if (!lead) return fail(nullptr, ICWF_EINVAL, "icwf_step_batch: NULL simulation");
+    std::string key;
+    if (!batch_key(lead, &key))
+        return fail(lead, ICWF_EINVAL, "icwf_step_batch: this simulation steps alone (padded N >= 1024, explicit "
+                                       "inverses or per-kernel timing)");
+    for (int k = 0; k < n_sims; ++k) {
+        icwf_sim *s = sims[k];
+        std::string kk;
+        if (!s) return fail(lead, ICWF_EINVAL, "icwf_step_batch: NULL simulation");
+        for (int q = 0; q < k; ++q)
+            if (sims[q] == s) return fail(lead, ICWF_EINVAL, "icwf_step_batch: a simulation appears twice");
+        if (s->status != ICWF_OK) return fail(s, ICWF_ESTATE, "the simulation stopped on an earlier error");
+        if (!batch_key(s, &kk) || kk != key)
+            return fail(lead, ICWF_EINVAL, "icwf_step_batch: the simulations differ in shape or parameters the "
+                                           "launches share");
+        if (s->stream != lead->stream) return fail(lead, ICWF_EINVAL, "icwf_step_batch: the simulations must share a stream");
+        if (s->parity != lead->parity) return fail(lead, ICWF_EINVAL, "icwf_step_batch: the simulations are at steps of different parity");
+    }
+    // simulations whose couplings differ in whether a sum of products is the
+    // whole contraction step in a batch for each
+    std::vector<icwf_sim *> group[2];
+    for (int k = 0; k < n_sims; ++k) group[sims[k]->d.products ? 1 : 0].push_back(sims[k]);
+    for (auto &g : group) {
+        const icwf_status st = step_group(g, n_steps);
+        if (st != ICWF_OK) {
+            if (!g.empty() && g[0] != lead) lead->err = g[0]->err;
+            return st;
         }
     }
     return ICWF_OK;

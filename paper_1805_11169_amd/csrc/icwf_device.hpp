@@ -100,9 +100,13 @@ __device__ inline int mfma_row(float, int lane, int v) { return mfma_row_f32(lan
 // zoff == nullptr: one simulation, no offset.
 __device__ inline long long batch_offset(const long long *zoff, int z) { return zoff ? zoff[z] : 0; }
 __device__ inline long long batch_offset(const long long *zoff) { return batch_offset(zoff, blockIdx.z); }
+// (Through the global address space: from a plain integer the compiler would
+// take the result for a generic pointer and use flat loads, which wait on the
+// LDS counter as well.)
 template <typename T>
 __device__ inline T *zshift(T *p, long long o) {
-    return p ? reinterpret_cast<T *>(reinterpret_cast<uintptr_t>(p) + static_cast<uintptr_t>(o)) : p;
+    typedef __attribute__((address_space(1))) T global_t;
+    return p ? (T *)reinterpret_cast<global_t *>(reinterpret_cast<uintptr_t>(p) + static_cast<uintptr_t>(o)) : p;
 }
 
 // Device status flags (one int32 each, in the workspace).

@@ -15,7 +15,8 @@ namespace icwf {
 
 struct Dims {
     int N, nr, nR, n_bo, prec;
-    int lr_rank;                          // rank of the FP64 part of the mixed contraction
+    int lr_rank;                          // terms of the sum of products of W_c the contraction uses
+    int products;                         // the contraction is that sum alone (exact to the table's rounding)
     int fp32_residual;                    // mixed form: the residual left to FP32 is not negligible
     int sinv;                             // RK4 stages through explicit inverses of S + eps I
     int propagator;                       // 0 split operator, 1 Crank-Nicolson
@@ -72,7 +73,10 @@ struct Bufs {
     double2 *tw_r, *tw_R;                 // exp(-2 pi i k / n)
     double *wc64;                         // [nr][nR] W_c(r_i, R_j)
     float *wc32;                          // [nr][nR] FP32 residual of the rank-K split (mixed form)
-    double *lr_u, *lr_v;                  // [kLowRankMax][nr], [kLowRankMax][nR] rank-K factors
+    double *lr_u, *lr_v;                  // rank-K factors in blocks of 16 ranks, [4][nr / 2][16][2] and
+                                          // [4][nR / 2][16][2] (point i of rank k: block k / 16, pair i / 2,
+                                          // k % 16, i % 2), as the contraction's lanes read them
+    int32_t *lr_pad;                      // K rounded up to whole blocks of 16
     float2 *psi1_f32;                     // [Np][nr] FP32 copy of psi1 (mixed form only)
     double *sinc_r, *dsinc_r;             // [N][nr] periodic sinc and derivative at r^a
     double *sinc_R, *dsinc_R;             // [N][nR]

@@ -89,16 +89,16 @@ struct icwf_server {
 namespace {
 
 // Estimated device time of one step (ms): a launch-bound floor plus the
-// step's flops at a sustained 40 TFLOP/s (the two-body contraction, dense or
-// through its rank factors, the single-species products and velocities, two
-// complex factorisations).  Only ratios between simulations matter: the
+// step's flops at a sustained 40 TFLOP/s (the two-body contraction, dense or,
+// where that is less, through some 32 rank factors, the single-species
+// products and velocities, two complex factorisations).  Only ratios between simulations matter: the
 // scheduler gives every simulation turns of about the same device time.
 double step_cost_ms(const icwf_config &c) {
     const double N = (double)((c.n_traj + 63) / 64 * 64), nr = c.n_r, nR = c.n_R;
     const double pairs = 0.5 * N * (N + 1.0);
     double contraction = 4.0 * pairs * nr * nR;
-    if (c.precision == ICWF_PREC_MIXED) contraction *= 0.6;
-    if (c.precision == ICWF_PREC_SEPARABLE) contraction = 4.0 * pairs * (nr + nR) * 32.0;
+    const double products = 4.0 * pairs * (nr + nR) * 32.0;
+    if (c.precision == ICWF_PREC_SEPARABLE || products < contraction) contraction = products;
     const double rest = 28.0 * N * N * (nr + nR) + 2.0 * (8.0 / 3.0) * N * N * N;
     return 0.4 + (contraction + rest) / 4e10;
 }

@@ -558,94 +558,187 @@ __global__ void __launch_bounds__(256, 2) k_wc(const typename WcTraits<T>::cplx 
 //     Wc[b][a] (+)= hr hR sum_k alpha_k(b, a) beta_k(b, a),
 //     alpha_k(b, a) = sum_i conj(psi1^b_i) psi1^a_i u_k(r_i),
 //     beta_k(b, a)  = sum_j conj(psi2^b_j) psi2^a_j v_k(R_j),
-// for W_c ~ sum_k u_k(r) v_k(R).  The pair tiles, queue, staging and pair
-// products of k_wc, with the W_c table replaced by 16 rank factors at a time:
-// MFMA rows = a, columns = the rank k of the chunk, reduction over i (then j
-// with the psi2 rows); the epilogue multiplies the two products and sums over
-// the chunk's ranks with 16-lane shuffles.  Ranks above K have zero factors.
-constexpr int kSepKC = 32;   // grid points per staged chunk
+// for W_c ~ sum_k u_k(r) v_k(R).  MFMA rows = a, columns = 16 ranks k,
+// reduction over the grid points; the A operand, the pair product, is formed
+// in registers and feeds RB column blocks of ranks.  Ranks above K have zero
+// factors.
+//
+// A unit is 16 a x B b.  The four waves of its work-group take the 8-point
+// steps of the grid in turn: each sums a quarter of every stretch of it, so
+// the four partial sums are of one size and their chains of roundings a
+// quarter as long (Wc against 80-bit sums, rms over pairs relative to max |Wc|:
+// 1.8e-16 at 512 x 256, K = 28, where the dense table's sum has 1.9e-16; 2.1e-16
+// and 3.3e-16 at 1024 x 512; 0.9e-16 and 1.2e-16 for the cavity's K = 1).
+// They read their operands straight from global memory, two consecutive
+// points per lane: no staging through LDS and no barrier inside a pass, so a
+// wave only waits for its own loads, which are issued one step ahead.  Only
+// the partial sums meet in LDS, 32 KB at a time.  Matrix cores bound it (16
+// products per 16 pair-product operations): 0.57 of the FP64 peak on 32 ranks
+// at N = 512, 512 x 256, 0.73 at 4096 x 256, where a unit's sums are longer
+// against its two reductions.
+typedef double dbl2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(1))) char gchar;
+typedef __attribute__((address_space(1))) dbl2 gdouble2;
 
-// One factor product of a rank chunk: acc[bb][re/im] (rows a, columns k) =
-// sum_i conj(X^b_i) X^a_i F[k0 + k][i] for the wave's four b rows.
-__device__ inline void sep_pass(dbl4 (&acc)[4][2], const double2 *__restrict__ X, const double *__restrict__ F,
-                                int n, int k0, int a_base, int b_tile, double2 (*sA)[32][kSepKC + 1],
-                                double (*sF)[kSepKC][17]) {
-    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-    const int row = lane & 15, quarter = lane >> 4;
-    constexpr int QS = kSepKC / 4;
-#pragma unroll
-    for (int bb = 0; bb < 4; ++bb) {
-        acc[bb][0] = dbl4{0, 0, 0, 0};
-        acc[bb][1] = dbl4{0, 0, 0, 0};
+// A wave-uniform global address whose origin the compiler cannot see, and a
+// point that loads through it are not moved across: without the two it sinks
+// the loads of the next step down to their use.
+__device__ __forceinline__ const gchar *opaque(const void *p) {
+    uint64_t u = reinterpret_cast<uint64_t>(p);
+    asm volatile("" : "+s"(u));
+    return reinterpret_cast<const gchar *>(u);
+}
+__device__ __forceinline__ void pin_loads() { asm volatile("" ::: "memory"); }
+
+constexpr int kSepWaves = 4;
+
+// Operand loads of one wave's steps of one species: uniform bases plus lane
+// offsets in bytes; step s takes the points 8 s + 2 quarter and
+// 8 s + 2 quarter + 1.
+template <int B, int RB>
+struct SepOperands {
+    const gchar *xa_at, *xb_at, *f_at;
+    uint32_t xoff, boff, foff, brow, frb;
+    dbl2 xa[2], xb[B][2], f[RB];
+
+    __device__ __forceinline__ static dbl2 ld(const gchar *base, uint32_t off) {
+        return *reinterpret_cast<const gdouble2 *>(base + off);
     }
-    const int nchunk = n / kSepKC;
-    // staging: element e = t + 256 m of the 32 psi rows x 32 points (m < 4) and
-    // of the 32 points x 16 ranks of the factors (m < 2)
-    double2 ra0, ra1, ra2, ra3;
-    double rf0, rf1;
-    const int rr0 = t >> 5, cc = t & 31;
-    const int ii0 = t >> 4, kk = t & 15;
-    const double2 *xrow[4];
+    __device__ __forceinline__ void load(dbl2 (&of)[RB]) {
+        xa[0] = ld(xa_at, xoff);
+        xa[1] = ld(xa_at, xoff + 16u);
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        const int rr = rr0 + 8 * m;
-        xrow[m] = X + (size_t)(rr < 16 ? a_base + rr : b_tile + rr - 16) * n + cc;
-    }
-    const double *frow = F + (size_t)(k0 + kk) * n + ii0;
-    ra0 = xrow[0][0];
-    ra1 = xrow[1][0];
-    ra2 = xrow[2][0];
-    ra3 = xrow[3][0];
-    rf0 = frow[0];
-    rf1 = frow[16];
-    sA[0][rr0][cc] = ra0;
-    sA[0][rr0 + 8][cc] = ra1;
-    sA[0][rr0 + 16][cc] = ra2;
-    sA[0][rr0 + 24][cc] = ra3;
-    sF[0][ii0][kk] = rf0;
-    sF[0][ii0 + 16][kk] = rf1;
-    __syncthreads();
-    for (int ch = 0; ch < nchunk; ++ch) {
-        const int buf = ch & 1;
-        const bool more = ch + 1 < nchunk;
-        if (more) {
-            const int o = (ch + 1) * kSepKC;
-            ra0 = xrow[0][o];
-            ra1 = xrow[1][o];
-            ra2 = xrow[2][o];
-            ra3 = xrow[3][o];
-            rf0 = frow[o];
-            rf1 = frow[o + 16];
+        for (int rb = 0; rb < RB; ++rb) of[rb] = ld(f_at + (size_t)rb * frb, foff);
+#pragma unroll
+        for (int bb = 0; bb < B; ++bb) {
+            xb[bb][0] = ld(xb_at + (size_t)bb * brow, boff);
+            xb[bb][1] = ld(xb_at + (size_t)bb * brow, boff + 16u);
         }
-#pragma unroll 2
-        for (int s = 0; s < QS; ++s) {
-            const int col = quarter * QS + s;
-            const double2 xa = sA[buf][row][col];
-            const double f = sF[buf][col][row];
+        pin_loads();
+    }
+    // the loads of step lo (n >= 32: every wave has a step)
+    __device__ __forceinline__ void begin(const double2 *X, const double *F, int n, int k0, int a_base, int b_base,
+                                          int lo) {
+        const int lane = threadIdx.x & 63, row = lane & 15, quarter = lane >> 4;
+        xa_at = opaque(X + (size_t)a_base * n + (size_t)lo * 8);
+        xb_at = opaque(X + (size_t)b_base * n + (size_t)lo * 8);
+        f_at = opaque(F + (size_t)k0 * n + (size_t)lo * 128);
+        xoff = (uint32_t)row * n * 16u + quarter * 32u;
+        boff = quarter * 32u;
+        foff = (uint32_t)lane * 16u;
+        brow = 16u * n;
+        frb = 128u * n;
+        load(f);
+    }
+    // `count` steps, every kSepWaves-th from the first
+    __device__ __forceinline__ void accumulate(dbl4 (&acc)[B][2][RB], int count) {
 #pragma unroll
-            for (int bb = 0; bb < 4; ++bb) {
-                const double2 p = cmulc(sA[buf][16 + 4 * wave + bb][col], xa);   // conj(X^b_i) X^a_i
-                acc[bb][0] = mfma(p.x, f, acc[bb][0]);
-                acc[bb][1] = mfma(p.y, f, acc[bb][1]);
+        for (int bb = 0; bb < B; ++bb)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) acc[bb][c][rb] = dbl4{0, 0, 0, 0};
+        // a step: the pair products of its two points, then its loads'
+        // registers take the next step's operands while the matrix cores work
+        auto step = [&](dbl2 (&fc)[RB], dbl2 (&fn)[RB], bool last) __attribute__((always_inline)) {
+            double pr[B][2], pi[B][2];
+#pragma unroll
+            for (int bb = 0; bb < B; ++bb)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {        // conj(X^b) X^a
+                    pr[bb][e] = fma(xb[bb][e].y, xa[e].y, xb[bb][e].x * xa[e].x);
+                    pi[bb][e] = fma(-xb[bb][e].y, xa[e].x, xb[bb][e].x * xa[e].y);
+                }
+            const size_t st = last ? 0 : 128 * kSepWaves;   // the last step loads its own operands again (never used)
+            xa_at += st;
+            xb_at += st;
+            f_at += 8 * st;
+            load(fn);
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int bb = 0; bb < B; ++bb)
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb) {
+                        acc[bb][0][rb] = mfma(pr[bb][e], fc[rb][e], acc[bb][0][rb]);
+                        acc[bb][1][rb] = mfma(pi[bb][e], fc[rb][e], acc[bb][1][rb]);
+                    }
+        };
+        dbl2 g[RB];
+        int s = 0;
+        for (; s + 1 < count; s += 2) {
+            step(f, g, false);
+            step(g, f, s + 2 >= count);
+        }
+        if (s < count) step(f, g, true);
+    }
+};
+
+// LDS of a work-group: the partial sums of one round, the alphas of the pass,
+// and the running sums over the ranks of each column block.
+template <int B>
+struct SepShared {
+    static constexpr int W = kSepWaves, ROUND = 32 / W;   // items per round
+    double2 red[W][ROUND][64];
+    double2 alpha[8 * B][64];
+    double2 wl[2][B][16];
+};
+
+// One pass over RB blocks of 16 ranks from k0.  Items (bb, rb, v): one
+// accumulator register pair (re, im) of every lane; item j is summed over the
+// waves by wave j mod W.
+template <int B, int RB>
+__device__ __forceinline__ void sep_pass(SepShared<B> &sh, const double2 *__restrict__ psi1,
+                                         const double2 *__restrict__ psi2, const double *__restrict__ U,
+                                         const double *__restrict__ V, int nr, int nR, int k0, int a_base,
+                                         int b_base) {
+    const int lane = threadIdx.x & 63, row = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    constexpr int W = kSepWaves, T = 4 * B * RB, IPR = SepShared<B>::ROUND < T ? SepShared<B>::ROUND : T;
+    dbl4 acc[B][2][RB];
+    SepOperands<B, RB> op;
+    const int steps1 = nr >> 3, steps2 = nR >> 3;
+    op.begin(psi1, U, nr, k0, a_base, b_base, wave);
+#pragma unroll
+    for (int sp = 0; sp < 2; ++sp) {
+        const int steps = sp ? steps2 : steps1;
+        op.accumulate(acc, steps / W);
+        // the second species' first loads are in flight over the reduction
+        if (sp == 0) op.begin(psi2, V, nR, k0, a_base, b_base, wave);
+#pragma unroll
+        for (int r = 0; r < T / IPR; ++r) {
+            __syncthreads();                         // the previous round's sums are read
+#pragma unroll
+            for (int j = 0; j < IPR; ++j) {
+                const int it = r * IPR + j, bb = it / (4 * RB), rb = (it / 4) % RB, v = it & 3;
+                sh.red[wave][j][lane] = make_double2(acc[bb][0][rb][v], acc[bb][1][rb][v]);
+            }
+            __syncthreads();
+            for (int j = wave; j < IPR; j += W) {
+                const int it = r * IPR + j;
+                const double2 x = cadd(cadd(sh.red[0][j][lane], sh.red[1][j][lane]),
+                                       cadd(sh.red[2][j][lane], sh.red[3][j][lane]));
+                if (sp == 0) {
+                    sh.alpha[it][lane] = x;          // read back by this wave only
+                } else {
+                    const int bb = it / (4 * RB), rb = (it / 4) % RB, v = it & 3;
+                    const double2 al = sh.alpha[it][lane];
+                    const double2 p = make_double2(fma(-al.y, x.y, al.x * x.x), fma(al.y, x.x, al.x * x.y));
+                    const double2 y = make_double2(row16_sum(p.x), row16_sum(p.y));
+                    if (row == 0) {
+                        double2 &dst = sh.wl[rb][bb][mfma_row_f64(lane, v)];
+                        dst = cadd(dst, y);
+                    }
+                }
             }
         }
-        if (more) {
-            const int nb = buf ^ 1;
-            sA[nb][rr0][cc] = ra0;
-            sA[nb][rr0 + 8][cc] = ra1;
-            sA[nb][rr0 + 16][cc] = ra2;
-            sA[nb][rr0 + 24][cc] = ra3;
-            sF[nb][ii0][kk] = rf0;
-            sF[nb][ii0 + 16][kk] = rf1;
-        }
-        __syncthreads();
     }
 }
 
-template <bool BATCHED>
-__global__ void __launch_bounds__(256, 2) k_wc_sep(const double2 *__restrict__ psi1, const double2 *__restrict__ psi2,
+template <int B, bool BATCHED>
+__global__ void __launch_bounds__(64 * kSepWaves, 2) k_wc_sep(const double2 *__restrict__ psi1, const double2 *__restrict__ psi2,
                                                    const double *__restrict__ U, const double *__restrict__ V,
-                                                   int kpad, int nr, int nR, double scale,
+                                                   const int32_t *__restrict__ kpad_at, int nr, int nR, double scale,
                                                    double2 *__restrict__ Wc, int Np, int accumulate, int ntiles,
                                                    int32_t *__restrict__ queue, const int32_t *__restrict__ order,
                                                    const int32_t *__restrict__ flags, const long long *__restrict__ zoff) {
@@ -654,69 +747,63 @@ __global__ void __launch_bounds__(256, 2) k_wc_sep(const double2 *__restrict__ p
     psi2 = zshift(psi2, zo_);
     U = zshift(U, zo_);
     V = zshift(V, zo_);
+    kpad_at = zshift(kpad_at, zo_);
     Wc = zshift(Wc, zo_);
     queue = zshift(queue, zo_);
     order = zshift(order, zo_);
     flags = zshift(flags, zo_);
 
     if (flags[kFlagHalt]) return;
-    __shared__ double2 sA[2][32][kSepKC + 1];
-    __shared__ double sF[2][kSepKC][17];
-    __shared__ double2 wl[4][4][16];     // [wave][b][a] block partial of Wc
-    __shared__ int s_tile;
-    // tiles from the per-XCD queues over the blocked tile order, as k_wc
+    __shared__ SepShared<B> sh;
+    __shared__ int s_unit;
+    const int kpad = __builtin_amdgcn_readfirstlane(*kpad_at);
+    constexpr int G = 16 / B;                        // units per tile
+    const int units = ntiles * G;
+    const bool queued = (int)gridDim.x < units;      // else one unit per work-group
+    // units from the per-XCD queues over the blocked tile order, as k_wc
     const int xcd = __builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)) & (kWcQueues - 1);   // HW_REG_XCC_ID
+    auto take = [&] {
+        int got = -1;
+        for (int o = 0; o < kWcQueues && got < 0; ++o) {
+            const int q = (xcd + o) & (kWcQueues - 1);
+            const int lo = (int)((long long)q * units / kWcQueues);
+            const int n = (int)((long long)(q + 1) * units / kWcQueues) - lo;
+            if (__hip_atomic_load(&queue[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= n) continue;
+            const int k = atomicAdd(&queue[q], 1);
+            if (k < n) got = lo + k;
+        }
+        return got;
+    };
+    int unit = blockIdx.x;
+    if (queued) {
+        if (threadIdx.x == 0) s_unit = take();
+        __syncthreads();
+        unit = s_unit;
+    }
     for (;;) {
-        if (threadIdx.x == 0) {
-            int got = -1;
-            for (int o = 0; o < kWcQueues && got < 0; ++o) {
-                const int q = (xcd + o) & (kWcQueues - 1);
-                const int lo = (int)((long long)q * ntiles / kWcQueues);
-                const int n = (int)((long long)(q + 1) * ntiles / kWcQueues) - lo;
-                if (__hip_atomic_load(&queue[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= n) continue;
-                const int k = atomicAdd(&queue[q], 1);
-                if (k < n) got = lo + k;
-            }
-            s_tile = got;
-        }
-        __syncthreads();
-        const int pos = s_tile;
-        __syncthreads();
-        if (pos < 0) break;
+        unit = __builtin_amdgcn_readfirstlane(unit);
+        if (unit < 0 || unit >= units) break;
+        __syncthreads();                             // s_unit is read
+        if (queued && threadIdx.x == 64 * (kSepWaves - 1)) s_unit = take();   // the next unit, while this one is worked on
         int tb, ta;
-        triangle_tile(order[pos], &tb, &ta);
-        const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-        const int row = lane & 15;
-        const int a_base = ta * 16, b_tile = tb * 16, b_base = b_tile + 4 * wave;
-        wl[wave][lane >> 4][lane & 15] = make_double2(0, 0);
-        for (int k0 = 0; k0 < kpad; k0 += 16) {
-            dbl4 acc1[4][2], acc2[4][2];
-            sep_pass(acc1, psi1, U, nr, k0, a_base, b_tile, sA, sF);
-            sep_pass(acc2, psi2, V, nR, k0, a_base, b_tile, sA, sF);
-#pragma unroll
-            for (int bb = 0; bb < 4; ++bb)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    // lane: a = a_base + mfma_row(lane, v), rank k0 + row
-                    double2 x = cmul(make_double2(acc1[bb][0][v], acc1[bb][1][v]),
-                                     make_double2(acc2[bb][0][v], acc2[bb][1][v]));
-#pragma unroll
-                    for (int off = 8; off > 0; off >>= 1) {
-                        x.x += __shfl_xor(x.x, off, 16);
-                        x.y += __shfl_xor(x.y, off, 16);
-                    }
-                    if (row == 0) {
-                        double2 &dst = wl[wave][bb][mfma_row_f64(lane, v)];
-                        dst = cadd(dst, x);
-                    }
-                }
-        }
-        {
-            const int bb = lane >> 4, a = lane & 15;
-            const double2 x = cscale(wl[wave][bb][a], scale);
+        triangle_tile(order[unit / G], &tb, &ta);
+        const int a_base = __builtin_amdgcn_readfirstlane(ta * 16);
+        const int b_base = __builtin_amdgcn_readfirstlane(tb * 16 + (unit % G) * B);
+        const int t = threadIdx.x;
+        if (t < 2 * B * 16) (&sh.wl[0][0][0])[t] = make_double2(0, 0);
+        int k0 = 0;
+        for (; k0 + 32 <= kpad; k0 += 32) sep_pass<B, 2>(sh, psi1, psi2, U, V, nr, nR, k0, a_base, b_base);
+        if (k0 < kpad) sep_pass<B, 1>(sh, psi1, psi2, U, V, nr, nR, k0, a_base, b_base);
+        __syncthreads();
+        if (t < B * 16) {
+            const int bb = t >> 4, a = t & 15;
+            const double2 x = cscale(cadd(sh.wl[0][bb][a], sh.wl[1][bb][a]), scale);
             double2 *dst = Wc + (size_t)(b_base + bb) * Np + a_base + a;
             *dst = accumulate ? cadd(*dst, x) : x;
         }
+        if (!queued) break;
+        __syncthreads();                             // wl is read
+        unit = s_unit;
     }
 }
 
@@ -800,6 +887,25 @@ void launch_single_species_next(const Dims &d, const Bufs &b, hipStream_t s) {
                        zb, Np, b.flags, 2, d.zoff);
 }
 
+// The sum-of-products contraction.  Fewer b per unit where the launch would
+// otherwise leave compute units without work; the sums of a pair do not depend
+// on it (512 x 256, K = 28: N = 64, 16 us with 1, 22 with 2, 36 with 4; N = 250,
+// 159, 107 and 117 us; N = 500, 550, 340 and 305 us).
+static void launch_wc_sep(const Dims &d, const Bufs &b, int accumulate, hipStream_t s) {
+    const int Np = padded(d.N), T16 = Np / 16, tiles = T16 * (T16 + 1) / 2;
+    auto go = [&](auto kernel, int B) {
+        const int units = tiles * (16 / B), grid = std::min(units, d.wc_grid);
+        if (grid < units) launch_fill_i32(b.wc_queue, kWcQueues, 0, s, d.batch, d.zoff);
+        hipLaunchKernelGGL(kernel, dim3(grid, 1, d.batch), dim3(64 * kSepWaves), 0, s, b.psi1, b.psi2, b.lr_u, b.lr_v,
+                           b.lr_pad, d.nr, d.nR, d.hr * d.hR, b.Wc, Np, accumulate, tiles, b.wc_queue, b.wc_order,
+                           b.flags, d.zoff);
+    };
+    const long long all = (long long)tiles * d.batch;
+    if (all * 16 <= 512) go(d.zoff ? k_wc_sep<1, true> : k_wc_sep<1, false>, 1);
+    else if (all * 4 <= 768) go(d.zoff ? k_wc_sep<2, true> : k_wc_sep<2, false>, 2);
+    else go(d.zoff ? k_wc_sep<4, true> : k_wc_sep<4, false>, 4);
+}
+
 void launch_wc(const Dims &d, const Bufs &b, hipStream_t s) {
     const int Np = padded(d.N);
     const int T16 = Np / 16;
@@ -817,28 +923,16 @@ void launch_wc(const Dims &d, const Bufs &b, hipStream_t s) {
     // the FP32 pass tiles the grid in chunks of 64 x 64 points: smaller grids
     // take the dense FP64 contraction of the whole table instead
     const bool fp32_fits = d.nr >= WcChunk<float>::KC && d.nR >= WcChunk<float>::JT;
-    if (d.prec == 1 && fp32_fits) {
+    if (d.products) {
+        launch_wc_sep(d, b, 0, s);
+    } else if (d.prec == 1 && fp32_fits) {
         // mixed: FP32 matrix cores on the residual of the rank-K split, FP64 rank-K part added
-        // (the FP32 pass only where the residual is above the table's rounding)
-        if (d.fp32_residual) {
-            split(WcChunk<float>::JT, &nparts, &spq);
-            launch_fill_i32(b.wc_queue, kWcQueues + kWcQueues * spq, 0, s, d.batch, d.zoff);
-            hipLaunchKernelGGL((d.zoff ? k_wc<float, true> : k_wc<float, false>), dim3(grid, 1, d.batch), dim3(256), 0, s, b.psi1_f32, b.psi2, b.wc32, d.nr,
-                               d.nR, scale, b.Wc, Np, 0, blocks, spq, nparts, b.wc_queue, b.wc_order, b.wc_part,
-                               b.flags, d.zoff);
-        }
-        if (d.lr_rank > 0) {
-            launch_fill_i32(b.wc_queue, kWcQueues, 0, s, d.batch, d.zoff);
-            hipLaunchKernelGGL(d.zoff ? k_wc_sep<true> : k_wc_sep<false>, dim3(std::min(blocks, d.wc_grid), 1, d.batch), dim3(256), 0, s, b.psi1,
-                               b.psi2, b.lr_u, b.lr_v, (d.lr_rank + 15) / 16 * 16, d.nr, d.nR, scale, b.Wc, Np,
-                               d.fp32_residual ? 1 : 0, blocks, b.wc_queue, b.wc_order, b.flags, d.zoff);
-        }
-    } else if (d.prec == 2) {
-        // separable: the whole contraction through the sum of products (assigns Wc)
-        launch_fill_i32(b.wc_queue, kWcQueues, 0, s, d.batch, d.zoff);
-        hipLaunchKernelGGL(d.zoff ? k_wc_sep<true> : k_wc_sep<false>, dim3(std::min(blocks, d.wc_grid), 1, d.batch), dim3(256), 0, s, b.psi1, b.psi2,
-                           b.lr_u, b.lr_v, (d.lr_rank + 15) / 16 * 16, d.nr, d.nR, scale, b.Wc, Np, 0, blocks,
-                           b.wc_queue, b.wc_order, b.flags, d.zoff);
+        split(WcChunk<float>::JT, &nparts, &spq);
+        launch_fill_i32(b.wc_queue, kWcQueues + kWcQueues * spq, 0, s, d.batch, d.zoff);
+        hipLaunchKernelGGL((d.zoff ? k_wc<float, true> : k_wc<float, false>), dim3(grid, 1, d.batch), dim3(256), 0, s,
+                           b.psi1_f32, b.psi2, b.wc32, d.nr, d.nR, scale, b.Wc, Np, 0, blocks, spq, nparts,
+                           b.wc_queue, b.wc_order, b.wc_part, b.flags, d.zoff);
+        if (d.lr_rank > 0) launch_wc_sep(d, b, 1, s);
     } else {
         split(WcChunk<double>::JT, &nparts, &spq);
         launch_fill_i32(b.wc_queue, kWcQueues + kWcQueues * spq, 0, s, d.batch, d.zoff);

@@ -11,11 +11,8 @@
 // the regularised matrices handed to the factorisation.
 //
 // Cholesky (lower, in place, two matrices per launch): right-looking with
-// 64-wide panels.  Each k_chol_panel work-group eliminates, column by column,
-// the 96 x 64 slab of the diagonal block and 32 of the rows below it, held
-// in registers (lane = column, wave = 8 rows; the pivot column through LDS,
-// one barrier per column); every work-group factors the diagonal block
-// itself, so the panel needs no communication between work-groups.
+// 64-wide panels.  k_chol_panel factors the diagonal block (every work-group
+// for itself), inverts it and solves for the rows below.
 // k_chol_update subtracts L21 L21^H from the trailing lower triangle on FP64
 // matrix cores.  A pivot that is not positive raises the solve flag.
 //
@@ -25,7 +22,7 @@
 // k_rk_fwd: a work-group solves L y = K v for its block after the blocks
 // above it are done (it waits on their flags and subtracts their
 // contributions as they arrive), then applies the inverse of its diagonal
-// block (from k_tri_inv, computed beside the two-body contraction).
+// block (from k_chol_panel).
 // k_rk_bwd: the same for L^H x = y from the bottom up, then the stage update
 // k = -i x of its rows.  Work-groups take blocks in ticket order, so a
 // work-group only ever waits on work-groups that are already running, and
@@ -121,13 +118,6 @@ __device__ inline void raise_solve(int32_t *flags) {
     atomicOr(&flags[kFlagHalt], 1);
 }
 
-// Packed lower-triangular tile of NB x NB entries in LDS, column-major:
-// entry (row k, column j), k >= j, at colofs(j) + k - j.
-__host__ __device__ constexpr int colofs(int j) { return j * NB - j * (j - 1) / 2; }
-// Row-major packing: entry (row j, column i), i <= j, at rowofs(j) + i.
-__host__ __device__ constexpr int rowofs(int j) { return j * (j + 1) / 2; }
-constexpr int kPacked = NB * (NB + 1) / 2;
-
 // Broadcast lane `src` (wave-uniform) of a double to the whole wave.
 __device__ inline double bcast(double v, int src) {
     const int lo = __builtin_amdgcn_readlane(__double2loint(v), src);
@@ -135,156 +125,307 @@ __device__ inline double bcast(double v, int src) {
     return __hiloint2double(hi, lo);
 }
 
-// The panel: the 64 x 64 diagonal block stacked on this work-group's 32 rows
-// below it (a 96 x 64 slab), eliminated column by column (right-looking):
-// step j takes the pivot d = sqrt(a_jj) and subtracts
-// l_rj conj(l_cj) = a_rj conj(a_cj) / d^2 from every later column c; column j
-// below the pivot is scaled by 1/d once, after the last step (its entries do
-// not change after step j, and the updates use the unscaled values).  On the
-// diagonal rows this is the Cholesky factor L11; on the rows below it is
-// x L11^H = a.
-// 768 threads: wave g owns slab rows 8 g .. 8 g + 7 (g < 8: diagonal-block
-// rows; g >= 8: 8 of the rows below), lane c owns column c; 8 entries per
-// thread in registers with static indices.  At step j a wave takes its rows'
-// column-j entries from lane j by readlane; the column-j entries of the
-// diagonal rows (the pivot and every lane's a_cj) come through LDS, written by
-// lane j of the diagonal waves as soon as their step j - 1 update is done, so
-// one barrier per step publishes them.  The update runs on every entry of a
-// lane's column, branch-free: entries above the diagonal of the block are
-// updated too but never read (the factor is written from the lower part only).
+// The panel at column kb: the 64 x 64 diagonal block L11 L11^H = A11, its
+// inverse, and the rows below, L21 = A21 L11^-H.  One work-group of four waves
+// per 64 rows below, and one more for the diagonal block's own results; each
+// factors the diagonal block itself, so the panel needs no communication
+// between work-groups.
 //
-// The factored diagonal block goes to a scratch tile, not into A: other
-// work-groups of the same launch may still be reading the unfactored block.
-// Work-group 0 of the next launch (or k_chol_flush after the last panel) copies
-// it into place.  32 rows below per work-group rather than 64 where the
-// launch's work-groups fit the CU slots left to the factorisations (the first
-// panel at N = 1024 takes 60 of the 64 the FP64 contraction leaves free):
-// a quarter fewer waves per SIMD issue each column's updates (the
-// factorisation stream at N = 1024: 3.87 -> 3.69 ms stretched); else 64, in
-// one round of work-groups rather than two.
-constexpr int kPanelRows = 8;                   // slab rows per wave
-constexpr int kPanelDiagWaves = NB / kPanelRows;
-constexpr int panel_threads(int below) { return 64 * (NB + below) / kPanelRows; }
+// The block is held in LDS as 16 x 16 tiles.  A block column of 16 is
+// eliminated by one wave without a barrier, lane = row (the 16 pivot rows and
+// up to 48 below them), its 16 columns in registers: the pivot and the pivot
+// rows' entries come by readlane, so a column costs a short chain (readlane,
+// reciprocal root, scaling) and the update of the columns after it.  The other
+// waves then update the tiles to the right on matrix cores, one wave inverting
+// the 16 x 16 triangle meanwhile.  The rows below are solved transposed,
+// L11 Z = A21^H, 16 rows per wave: the accumulator layout of a matrix product
+// is the layout of its right operand, so Z_J = L_JJ^-1 (A_J^H - sum_I L_JI Z_I)
+// runs from register to register.  What bounds it is the chain of 64 columns
+// (a panel 30-36 us alone, 65-71 us on a compute unit that also runs the
+// contraction, whose matrix products hold the FP64 pipe 64 cycles at a time):
+// two matrices at N = 64, all kernels of the factorisation, 105 -> 37 us
+// against one barrier and one LDS round trip per column, with the inverses and
+// the last copy in kernels of their own; N = 500, 658 -> 326 us; N = 1024
+// beside the contraction, 1.68 -> 1.42 ms.
+constexpr int kTiles = 10;       // 16 x 16 tiles (I, K), K <= I, of the block
+typedef double2 Tile[16][17];
+__device__ constexpr int tile_of(int I, int K) { return I * (I + 1) / 2 + K; }
 
-template <int BELOW>   // rows below the diagonal block per work-group: 32 or 64
-__global__ void __launch_bounds__(panel_threads(BELOW)) k_chol_panel(double2 *A0, double2 *A1, int Np, int kb,
-                                                              double2 *__restrict__ diag,
-                                                              int32_t *__restrict__ flags, const long long *__restrict__ zoff) {
+struct PanelShared {
+    Tile L[kTiles];              // the block's lower tiles
+    Tile inv[4];                 // inverses of its diagonal tiles
+    Tile x[4];                   // off-diagonal tiles of the block's inverse
+    double dinv[NB];
+};
+
+// acc += s X Y^H for 16 x 16 tiles in LDS, s = +-1
+__device__ __forceinline__ void tile_mul_h(dbl4 &re, dbl4 &im, const Tile &X, const Tile &Y, double s) {
+    const int lane = threadIdx.x & 63, row = lane & 15, quarter = lane >> 4;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const double2 x = cscale(X[row][4 * q + quarter], s), y = Y[row][4 * q + quarter];
+        re = mfma(x.x, y.x, re);
+        re = mfma(x.y, y.y, re);
+        im = mfma(x.y, y.x, im);
+        im = mfma(-x.x, y.y, im);
+    }
+}
+// acc += s X Z, Z in accumulator layout
+__device__ __forceinline__ void tile_mul(dbl4 &re, dbl4 &im, const Tile &X, dbl4 zre, dbl4 zim, double s) {
+    const int lane = threadIdx.x & 63, row = lane & 15, quarter = lane >> 4;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const double2 x = cscale(X[row][4 * q + quarter], s);
+        re = mfma(x.x, zre[q], re);
+        re = mfma(-x.y, zim[q], re);
+        im = mfma(x.x, zim[q], im);
+        im = mfma(x.y, zre[q], im);
+    }
+}
+// a tile in accumulator layout
+__device__ __forceinline__ void tile_load(dbl4 &re, dbl4 &im, const Tile &X) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const double2 x = X[mfma_row_f64(lane, v)][lane & 15];
+        re[v] = x.x;
+        im[v] = x.y;
+    }
+}
+__device__ __forceinline__ void tile_store(Tile &X, dbl4 re, dbl4 im) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) X[mfma_row_f64(lane, v)][lane & 15] = make_double2(re[v], im[v]);
+}
+
+// Columns 16 J .. 16 J + 15 of the block, by one wave; false if a pivot is not
+// positive.
+__device__ __forceinline__ bool eliminate_block(PanelShared &sh, int J) {
+    const int lane = threadIdx.x & 63, r = lane & 15, I = J + (lane >> 4);
+    const bool mine = I < 4;
+    Tile &T = sh.L[tile_of(mine ? I : J, J)];
+    double2 a[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c) a[c] = T[r][c];
+    bool ok = true;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        double piv = bcast(a[j].x, j);
+        ok = ok && piv > 0.0;
+        piv = piv > 0.0 ? piv : 1.0;
+        // 1/sqrt(piv) from the hardware estimate and two Newton steps
+        // y <- y (3 - piv y^2) / 2 (each squares the relative error)
+        double dinv = __builtin_amdgcn_rsq(piv);
+        dinv = dinv * fma(-0.5 * piv * dinv, dinv, 1.5);
+        dinv = dinv * fma(-0.5 * piv * dinv, dinv, 1.5);
+        a[j] = cscale(a[j], dinv);
+        sh.dinv[16 * J + j] = dinv;
+#pragma unroll
+        for (int c = j + 1; c < 16; ++c) {
+            const double lx = bcast(a[j].x, c), ly = bcast(a[j].y, c);
+            // a_rc -= l_rj conj(l_cj)
+            a[c].x = fma(-a[j].y, ly, fma(-a[j].x, lx, a[c].x));
+            a[c].y = fma(a[j].x, ly, fma(-a[j].y, lx, a[c].y));
+        }
+    }
+    // the diagonal tile: zero above the diagonal, the diagonal real
+    const int top = I == J ? r : 16;
+    if (mine)
+#pragma unroll
+        for (int c = 0; c < 16; ++c)
+            T[r][c] = make_double2(c > top ? 0.0 : a[c].x, c >= top ? 0.0 : a[c].y);
+    return ok;
+}
+
+// Inverse of the diagonal tile J by one wave, lane = row: with
+// y_r = e_r - sum_{k<r} L_rk x_k, row r of the inverse is x_r = y_r / L_rr; step
+// j takes row j's y by readlane and subtracts (L_rj / L_jj) y_j from the rows
+// below it.
+__device__ __forceinline__ void invert_tile(PanelShared &sh, int J) {
+    const int lane = threadIdx.x & 63, r = lane & 15;
+    const Tile &T = sh.L[tile_of(J, J)];
+    double2 y[16], l[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c) {
+        const double2 x = T[r][c];                   // zero above the diagonal
+        const double d = sh.dinv[16 * J + c];
+        l[c] = make_double2(c == r ? 0.0 : x.x * d, x.y * d);
+        y[c] = make_double2(c == r ? 1.0 : 0.0, 0.0);
+    }
+#pragma unroll
+    for (int j = 0; j < 15; ++j)
+#pragma unroll
+        for (int c = 0; c <= j; ++c) {
+            const double px = bcast(y[c].x, j), py = bcast(y[c].y, j);
+            y[c].x = fma(l[j].y, py, fma(-l[j].x, px, y[c].x));
+            y[c].y = fma(-l[j].y, px, fma(-l[j].x, py, y[c].y));
+        }
+    const double d = sh.dinv[16 * J + r];
+    if (lane < 16)
+#pragma unroll
+        for (int c = 0; c < 16; ++c) sh.inv[J][r][c] = cscale(y[c], d);
+}
+
+__global__ void __launch_bounds__(256, 2) k_chol_panel(double2 *A0, double2 *A1, int Np, int kb,
+                                                       double2 *__restrict__ diag, double2 *__restrict__ X0,
+                                                       double2 *__restrict__ X1, double2 *__restrict__ F0,
+                                                       double2 *__restrict__ F1, int32_t *__restrict__ flags,
+                                                       const long long *__restrict__ zoff) {
     const long long zo_ = batch_offset(zoff);
     A0 = zshift(A0, zo_);
     A1 = zshift(A1, zo_);
     diag = zshift(diag, zo_);
+    X0 = zshift(X0, zo_);
+    X1 = zshift(X1, zo_);
+    F0 = zshift(F0, zo_);
+    F1 = zshift(F1, zo_);
     flags = zshift(flags, zo_);
 
     if (flags[kFlagHalt]) return;
     // the panel is a latency chain that shares compute units with the
     // contraction on the other stream: its waves take the issue slots first
     __builtin_amdgcn_s_setprio(3);
-    __shared__ double2 lcol[2][NB];      // column j over the diagonal rows, unscaled, alternating with j
-    __shared__ double dpiv[NB], dinvs[NB];
+    __shared__ PanelShared sh;
     double2 *A = blockIdx.y ? A1 : A0;
+    const int t = threadIdx.x, lane = t & 63, row = lane & 15, quarter = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const bool own = blockIdx.x == gridDim.x - 1;    // this work-group keeps the diagonal block's results
+#pragma unroll
+    for (int I = 0; I < 4; ++I)
+#pragma unroll
+        for (int K = 0; K <= I; ++K)
+            sh.L[tile_of(I, K)][t >> 4][t & 15] = A[(size_t)(kb + 16 * I + (t >> 4)) * Np + kb + 16 * K + (t & 15)];
+    // the rows below, conjugate transposed, in accumulator layout: this lane
+    // has the row `row` of its wave's 16 and the columns 16 J + quarter + 4 v
+    double2 *arow = A + (size_t)(kb + NB + 64 * blockIdx.x + 16 * wave + row) * Np + kb + quarter;
+    dbl4 zre[4], zim[4];
+    auto load_rows = [&]() __attribute__((always_inline)) {
+        if (own) return;
+#pragma unroll
+        for (int J = 0; J < 4; ++J)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const double2 x = arow[16 * J + 4 * v];
+                zre[J][v] = x.x;
+                zim[J][v] = -x.y;
+            }
+    };
+    __syncthreads();
+    auto eliminate = [&](int J) {
+        if (!eliminate_block(sh, J) && own && lane == 0) raise_solve(flags);
+    };
+    for (int J = 0; J < 3; ++J) {
+        if (wave == 0) eliminate(J);
+        if (wave == 1 && J > 0) invert_tile(sh, J - 1);
+        __syncthreads();
+        // tiles (I, K), J < K <= I, over the waves
+        int n = 0;
+        for (int K = J + 1; K < 4; ++K)
+            for (int I = K; I < 4; ++I, ++n) {
+                if ((n & 3) != wave) continue;
+                dbl4 re, im;
+                tile_load(re, im, sh.L[tile_of(I, K)]);
+                tile_mul_h(re, im, sh.L[tile_of(I, J)], sh.L[tile_of(K, J)], -1.0);
+                tile_store(sh.L[tile_of(I, K)], re, im);
+            }
+        __syncthreads();
+    }
+    if (wave == 0) eliminate(3);
+    if (wave == 1) invert_tile(sh, 2);
+    if (wave > 1) load_rows();                       // in flight over the last block column
+    __syncthreads();
+    if (wave == 1) invert_tile(sh, 3);
+    if (wave < 2) load_rows();
+    __syncthreads();
+    if (!own) {
+#pragma unroll
+        for (int J = 0; J < 4; ++J) {
+#pragma unroll
+            for (int I = 0; I < J; ++I) tile_mul(zre[J], zim[J], sh.L[tile_of(J, I)], zre[I], zim[I], -1.0);
+            dbl4 re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+            tile_mul(re, im, sh.inv[J], zre[J], zim[J], 1.0);
+            zre[J] = re;
+            zim[J] = im;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) arow[16 * J + 4 * v] = make_double2(re[v], -im[v]);
+        }
+        return;
+    }
+    // the diagonal block's results.  The factored block goes to a scratch
+    // tile while other work-groups of the launch may still be reading the
+    // unfactored one; this work-group of the next launch copies it into place.
     double2 *D = diag + (size_t)blockIdx.y * NB * NB;
-    const int t = threadIdx.x, c = t & 63, g = t >> 6;
-    if (blockIdx.x == 0 && kb > 0) {
+    const bool last = kb + NB == Np;
+    if (kb > 0) {
         const int pb = kb - NB;
-        for (int e = t; e < NB * NB; e += panel_threads(BELOW)) {
+        for (int e = t; e < NB * NB; e += 256) {
             const int rr = e / NB, cc = e % NB;
             if (cc <= rr) A[(size_t)(pb + rr) * Np + pb + cc] = D[e];
         }
+        __syncthreads();                             // D is read before it is written again
     }
-    const bool below = kb + NB < Np;
-    const bool diagw = g < kPanelDiagWaves;
-    const bool mine = diagw || below;                 // rows below exist for this wave
-    const int srow = kPanelRows * g;                  // first slab row of this wave
-    const int grow = diagw ? kb + srow : kb + NB + blockIdx.x * BELOW + kPanelRows * (g - kPanelDiagWaves);
-    double2 a[kPanelRows];
 #pragma unroll
-    for (int v = 0; v < kPanelRows; ++v)
-        a[v] = mine ? A[(size_t)(grow + v) * Np + kb + c] : make_double2(0.0, 0.0);
-    if (c == 0 && diagw) {
+    for (int I = 0; I < 4; ++I)
 #pragma unroll
-        for (int v = 0; v < kPanelRows; ++v) lcol[0][srow + v] = a[v];
-    }
+        for (int K = 0; K <= I; ++K) {
+            const int rr = 16 * I + (t >> 4), cc = 16 * K + (t & 15);
+            const double2 x = sh.L[tile_of(I, K)][t >> 4][t & 15];
+            if (last) {
+                if (cc <= rr) A[(size_t)(kb + rr) * Np + kb + cc] = x;
+            } else {
+                D[rr * NB + cc] = x;
+            }
+        }
     __syncthreads();
-    bool bad = false;
-#pragma unroll 1
-    for (int j = 0; j < NB; ++j) {
-        const double2 *lj = lcol[j & 1];
-        double piv = lj[j].x;
-        const double2 lcj = lj[c];
-        double2 lr[kPanelRows];
-#pragma unroll
-        for (int v = 0; v < kPanelRows; ++v) lr[v] = make_double2(bcast(a[v].x, j), bcast(a[v].y, j));
-        if (!(piv > 0.0)) {
-            bad = true;
-            piv = 1.0;
+    // its inverse, by distance from the diagonal:
+    // X_IK = -X_II sum_{K<=M<I} L_IM X_MK
+    auto product = [&](int I, int K, auto tile, Tile &out) {
+        dbl4 re = {0, 0, 0, 0}, im = {0, 0, 0, 0}, ore = {0, 0, 0, 0}, oim = {0, 0, 0, 0};
+        for (int M = K; M < I; ++M) {
+            dbl4 xr, xi;
+            tile_load(xr, xi, tile(M, K));
+            tile_mul(re, im, sh.L[tile_of(I, M)], xr, xi, 1.0);
         }
-        // 1/sqrt(piv) from the hardware estimate and two Newton steps
-        // y <- y (3 - piv y^2) / 2 (each squares the relative error), then
-        // sqrt(piv) = piv y: a few FP64 operations instead of the correctly
-        // rounded sqrt and division sequences on the panel's serial chain
-        double dinv = __builtin_amdgcn_rsq(piv);
-        dinv = dinv * fma(-0.5 * piv * dinv, dinv, 1.5);
-        dinv = dinv * fma(-0.5 * piv * dinv, dinv, 1.5);
-        const double d = piv * dinv;
-        if (c > j) {
-            const double2 lc = cscale(cconj(lcj), dinv * dinv);
+        tile_mul(ore, oim, sh.inv[I], re, im, -1.0);
+        tile_store(out, ore, oim);
+    };
+    auto inverse = [&](int M, int K) -> Tile & {
+        if (M == K) return sh.inv[M];
+        if (M == K + 1) return sh.x[K];
+        return M == 2 ? sh.L[tile_of(2, 0)] : M - K == 2 ? sh.x[3] : sh.L[tile_of(3, 0)];
+    };
+    if (wave < 3) product(wave + 1, wave, inverse, sh.x[wave]);
+    __syncthreads();
+    if (wave == 0) product(2, 0, inverse, sh.L[tile_of(2, 0)]);
+    if (wave == 1) product(3, 1, inverse, sh.x[3]);
+    __syncthreads();
+    if (wave == 0) product(3, 0, inverse, sh.L[tile_of(3, 0)]);
+    __syncthreads();
+    double2 *X = blockIdx.y ? X1 : X0;
+    double2 *F = blockIdx.y ? F1 : F0;               // the same block in a full Np x Np inverse, or null
 #pragma unroll
-            for (int v = 0; v < kPanelRows; ++v) a[v] = csub(a[v], cmul(lr[v], lc));
-            if (c == j + 1 && diagw) {
-                double2 *ln = lcol[(j + 1) & 1];
+    for (int I = 0; I < 4; ++I)
 #pragma unroll
-                for (int v = 0; v < kPanelRows; ++v) ln[srow + v] = a[v];
-            }
-        } else if (t == j) {
-            dpiv[j] = d;
-            dinvs[j] = dinv;
+        for (int K = 0; K < 4; ++K) {
+            const int rr = 16 * I + (t >> 4), cc = 16 * K + (t & 15);
+            const double2 x = K <= I ? inverse(I, K)[t >> 4][t & 15] : make_double2(0.0, 0.0);
+            X[(size_t)(kb + rr) * NB + cc] = x;
+            if (F) F[(size_t)(kb + rr) * Np + kb + cc] = x;
         }
-        __syncthreads();
-    }
-    if (bad && t == 0 && blockIdx.x == 0) raise_solve(flags);
-    const double sc = dinvs[c];
-#pragma unroll
-    for (int v = 0; v < kPanelRows; ++v) a[v] = cscale(a[v], sc);
-    if (diagw) {
-        if (blockIdx.x == 0) {
-#pragma unroll
-            for (int v = 0; v < kPanelRows; ++v) {
-                const int r = srow + v;
-                if (r > c) D[r * NB + c] = a[v];
-                else if (r == c) D[r * NB + c] = make_double2(dpiv[c], 0.0);
-            }
-        }
-    } else if (below) {
-#pragma unroll
-        for (int v = 0; v < kPanelRows; ++v) A[(size_t)(grow + v) * Np + kb + c] = a[v];
-    }
-}
-
-__global__ void __launch_bounds__(256) k_chol_flush(double2 *A0, double2 *A1, int Np, int kb,
-                                                    const double2 *__restrict__ diag,
-                                                    const int32_t *__restrict__ flags, const long long *__restrict__ zoff) {
-    const long long zo_ = batch_offset(zoff);
-    A0 = zshift(A0, zo_);
-    A1 = zshift(A1, zo_);
-    diag = zshift(diag, zo_);
-    flags = zshift(flags, zo_);
-
-    if (flags[kFlagHalt]) return;
-    double2 *A = blockIdx.y ? A1 : A0;
-    const double2 *D = diag + (size_t)blockIdx.y * NB * NB;
-    for (int e = threadIdx.x; e < NB * NB; e += 256) {
-        const int rr = e / NB, cc = e % NB;
-        if (cc <= rr) A[(size_t)(kb + rr) * Np + kb + cc] = D[e];
-    }
 }
 
 // Trailing update A[i][k] -= sum_j L[i][j] conj(L[k][j]) over the lower
 // triangle i >= k of rows/cols kb+NB .. Np-1, j over the panel; one
 // work-group per 32 x 32 tile, wave w on its 16 x 16 fragment (w / 2, w % 2),
-// so a tile's 64-deep reduction runs on four matrix-core streams at once.
-__global__ void __launch_bounds__(256) k_chol_update(double2 *A0, double2 *A1, int Np, int kb,
-                                                     const int32_t *__restrict__ flags, const long long *__restrict__ zoff) {
+// so a tile's 64-deep reduction runs on four matrix-core streams at once.  A
+// lane takes two neighbouring columns j of its row per load pair (whole
+// 128-byte lines over its row's four lanes), all of them requested before the
+// first product: the launch is a few microseconds of latency and its products
+// (N = 1024: 40 -> 12 us beside the contraction, against 16-byte accesses 256
+// bytes apart, one product ahead).
+__global__ void __launch_bounds__(256, 2) k_chol_update(double2 *A0, double2 *A1, int Np, int kb,
+                                                        const int32_t *__restrict__ flags,
+                                                        const long long *__restrict__ zoff) {
     const long long zo_ = batch_offset(zoff);
     A0 = zshift(A0, zo_);
     A1 = zshift(A1, zo_);
@@ -302,150 +443,30 @@ __global__ void __launch_bounds__(256) k_chol_update(double2 *A0, double2 *A1, i
     const int f = wave >> 1, g = wave & 1;
     const int i0 = base + 32 * ti + 16 * f, k0 = base + 32 * tk + 16 * g;
     const int row = lane & 15, quarter = lane >> 4;
-    const int q = NB / 4;
+    const double2 *xp = A + (size_t)(i0 + row) * Np + kb + 2 * quarter;
+    const double2 *yp = A + (size_t)(k0 + row) * Np + kb + 2 * quarter;
+    double2 x[NB / 4], y[NB / 4], o[4];
+#pragma unroll
+    for (int s = 0; s < NB / 8; ++s)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            x[2 * s + e] = xp[8 * s + e];
+            y[2 * s + e] = yp[8 * s + e];
+        }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) o[v] = A[(size_t)(i0 + mfma_row_f64(lane, v)) * Np + k0 + row];
     dbl4 re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
-    const double2 *xp = A + (size_t)(i0 + row) * Np + kb + quarter * q;
-    const double2 *yp = A + (size_t)(k0 + row) * Np + kb + quarter * q;
-    for (int s = 0; s < q; ++s) {
-        const double2 xv = xp[s], yv = yp[s];
+#pragma unroll
+    for (int s = 0; s < NB / 4; ++s) {
         // x conj(y) = (xr yr + xi yi) + i (xi yr - xr yi)
-        re = mfma(xv.x, yv.x, re);
-        re = mfma(xv.y, yv.y, re);
-        im = mfma(xv.y, yv.x, im);
-        im = mfma(-xv.x, yv.y, im);
+        re = mfma(x[s].x, y[s].x, re);
+        im = mfma(x[s].y, y[s].x, im);
+        re = mfma(x[s].y, y[s].y, re);
+        im = mfma(-x[s].x, y[s].y, im);
     }
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int ii = i0 + mfma_row_f64(lane, v);
-        const int kk = k0 + row;
-        double2 *p = A + (size_t)ii * Np + kk;
-        const double2 o = *p;
-        *p = make_double2(o.x - re[v], o.y - im[v]);
-    }
-}
-
-// Inverse of each 64 x 64 diagonal block of a lower Cholesky factor,
-// X_B = L_BB^-1 (lower triangular), by block recursion:
-//     [[A, 0], [C, D]]^-1 = [[A^-1, 0], [-D^-1 C A^-1, D^-1]].
-// The four 16 x 16 diagonal blocks are inverted by the four waves at once
-// (lane c of wave w substitutes column c of its block in registers:
-// x_rc = (delta_rc - sum_{k<r} L_rk x_kc) / L_rr); the off-diagonal blocks of
-// the two 32 x 32 inverses, then the one of the 64 x 64 inverse, are the
-// products -D^-1 (C A^-1).  One work-group per block, a handful of barriers.
-// The stage solves apply X_B and X_B^H as matrix-vector products instead of a
-// 64-step substitution on their critical path.  Output: X[(B 64 + r) 64 + c].
-__global__ void __launch_bounds__(256) k_tri_inv(const double2 *__restrict__ A0, const double2 *__restrict__ A1,
-                                                 double2 *__restrict__ X0, double2 *__restrict__ X1,
-                                                 double2 *__restrict__ F0, double2 *__restrict__ F1, int Np,
-                                                 const int32_t *__restrict__ flags, const long long *__restrict__ zoff) {
-    const long long zo_ = batch_offset(zoff);
-    A0 = zshift(A0, zo_);
-    A1 = zshift(A1, zo_);
-    X0 = zshift(X0, zo_);
-    X1 = zshift(X1, zo_);
-    F0 = zshift(F0, zo_);
-    F1 = zshift(F1, zo_);
-    flags = zshift(flags, zo_);
-
-    if (flags[kFlagHalt]) return;
-    // 66.5 KB of LDS: fits beside a two-body contraction work-group on one CU
-    __shared__ double2 sX[NB][NB + 1];        // the inverse (lower; zero above)
-    const double2 *A = blockIdx.y ? A1 : A0;
-    double2 *X = blockIdx.y ? X1 : X0;
-    double2 *F = blockIdx.y ? F1 : F0;        // the same blocks in a full Np x Np inverse, or null
-    const int r0 = blockIdx.x * NB;
-    const double2 *Lb = A + (size_t)r0 * Np + r0;   // L_BB(r, k) = Lb[r Np + k]
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    for (int e = t; e < NB * (NB + 1); e += 256) sX[e / (NB + 1)][e % (NB + 1)] = make_double2(0.0, 0.0);
-    __syncthreads();
-    // 16 x 16 diagonal blocks (their entries are the same for every lane: cached loads)
-    if (lane < 16) {
-        const int c = lane, o = 16 * wave;
-        const double2 *Ld = Lb + (size_t)o * Np + o;
-        double2 x[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            double2 acc = make_double2(r == c ? 1.0 : 0.0, 0.0);
-#pragma unroll
-            for (int k = 0; k < r; ++k) acc = csub(acc, cmul(Ld[(size_t)r * Np + k], x[k]));
-            x[r] = cscale(acc, 1.0 / Ld[(size_t)r * Np + r].x);
-        }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sX[o + r][o + c] = x[r];
-    }
-    __syncthreads();
-    // level 1: blocks (1, 0) and (3, 2) of 16: T = L_ba X_aa into sX, then -X_bb T
-    {
-        const int p = t >> 7, u = t & 127;            // pair p, 128 threads per pair, 2 outputs each
-        const int a = 2 * p, bb = 2 * p + 1;
-        double2 o2[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int e = u + 128 * h, r = e >> 4, c = e & 15;
-            double2 acc = make_double2(0.0, 0.0);
-            for (int k = c; k < 16; ++k)
-                acc = cadd(acc, cmul(Lb[(size_t)(16 * bb + r) * Np + 16 * a + k], sX[16 * a + k][16 * a + c]));
-            o2[h] = acc;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int e = u + 128 * h, r = e >> 4, c = e & 15;
-            sX[16 * bb + r][16 * a + c] = o2[h];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int e = u + 128 * h, r = e >> 4, c = e & 15;
-            double2 acc = make_double2(0.0, 0.0);
-            for (int k = 0; k <= r; ++k) acc = cadd(acc, cmul(sX[16 * bb + r][16 * bb + k], sX[16 * bb + k][16 * a + c]));
-            o2[h] = make_double2(-acc.x, -acc.y);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int e = u + 128 * h, r = e >> 4, c = e & 15;
-            sX[16 * bb + r][16 * a + c] = o2[h];
-        }
-        __syncthreads();
-    }
-    // level 2: block (1, 0) of 32: T = L_BA X_AA, then -X_BB T (4 outputs per thread)
-    {
-        double2 o4[4];
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-            const int e = t + 256 * h, r = e >> 5, c = e & 31;
-            double2 acc = make_double2(0.0, 0.0);
-            for (int k = c; k < 32; ++k) acc = cadd(acc, cmul(Lb[(size_t)(32 + r) * Np + k], sX[k][c]));
-            o4[h] = acc;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-            const int e = t + 256 * h, r = e >> 5, c = e & 31;
-            sX[32 + r][c] = o4[h];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-            const int e = t + 256 * h, r = e >> 5, c = e & 31;
-            double2 acc = make_double2(0.0, 0.0);
-            for (int k = 0; k <= r; ++k) acc = cadd(acc, cmul(sX[32 + r][32 + k], sX[32 + k][c]));
-            o4[h] = make_double2(-acc.x, -acc.y);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-            const int e = t + 256 * h, r = e >> 5, c = e & 31;
-            sX[32 + r][c] = o4[h];
-        }
-        __syncthreads();
-    }
-    for (int e = t; e < NB * NB; e += 256) {
-        const int rr = e / NB, cc = e % NB;
-        X[(size_t)(r0 + rr) * NB + cc] = sX[rr][cc];
-        if (F) F[(size_t)(r0 + rr) * Np + r0 + cc] = sX[rr][cc];
-    }
+    for (int v = 0; v < 4; ++v)
+        A[(size_t)(i0 + mfma_row_f64(lane, v)) * Np + k0 + row] = make_double2(o[v].x - re[v], o[v].y - im[v]);
 }
 
 // ------------------------------------------------------------------ explicit inverse of L
@@ -637,7 +658,7 @@ __global__ void __launch_bounds__(256) k_matvec(const double2 *__restrict__ M, c
 }
 
 // Forward stage kernel: y_B = L_BB^-1 (rhs_B - sum_{C<B} L_BC y_C), with
-// L_BB^-1 from k_tri_inv.  256 threads; thread t: row i = t / 4 of the block,
+// L_BB^-1 from k_chol_panel.  256 threads; thread t: row i = t / 4 of the block,
 // quarter q = t % 4 of the columns.  Everything that does not depend on the
 // blocks above (the block's slices of L and of L_BB^-1) is loaded before the
 // waits.
@@ -919,35 +940,16 @@ void launch_assemble(const Dims &d, const Bufs &b, int parity, AssemblePart part
 void launch_cholesky(const Dims &d, const Bufs &b, double2 *A0, double2 *A1, double2 *X0, double2 *X1, int count,
                      hipStream_t s, double2 *F0, double2 *F1, double2 *H0, double2 *H1, bool inverses) {
     const int Np = padded(d.N);
-    // the CU slots the contraction leaves free (two work-groups per CU):
-    // 32 rows below per panel work-group where the first launch fits them
-    int dev = 0, ncu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu <= 0)
-        ncu = 256;
-    const int free_slots = std::max(2 * ncu - d.wc_grid, 1);
-    const bool narrow = (long long)count * d.batch * ((Np - NB) / 32) <= free_slots;
     for (int kb = 0; kb < Np; kb += NB) {
         const int below = Np - kb - NB;
-        if (narrow) {
-            const int gx = below > 0 ? below / 32 : 1;
-            hipLaunchKernelGGL(k_chol_panel<32>, dim3(gx, count, d.batch), dim3(panel_threads(32)), 0, s, A0, A1, Np,
-                               kb, b.chol_diag, b.flags, d.zoff);
-        } else {
-            const int gx = below > 0 ? below / 64 : 1;
-            hipLaunchKernelGGL(k_chol_panel<64>, dim3(gx, count, d.batch), dim3(panel_threads(64)), 0, s, A0, A1, Np,
-                               kb, b.chol_diag, b.flags, d.zoff);
-        }
+        hipLaunchKernelGGL(k_chol_panel, dim3(below / 64 + 1, count, d.batch), dim3(256), 0, s, A0, A1, Np, kb,
+                           b.chol_diag, X0, X1, F0, F1, b.flags, d.zoff);
         if (below > 0) {
             const int mt = below / 32;
             hipLaunchKernelGGL(k_chol_update, dim3(mt * (mt + 1) / 2, count, d.batch), dim3(256), 0, s, A0, A1, Np, kb,
                                b.flags, d.zoff);
         }
     }
-    hipLaunchKernelGGL(k_chol_flush, dim3(1, count, d.batch), dim3(256), 0, s, A0, A1, Np, Np - NB, b.chol_diag,
-                       b.flags, d.zoff);
-    hipLaunchKernelGGL(k_tri_inv, dim3(Np / NB, count, d.batch), dim3(256), 0, s, A0, A1, X0, X1, F0, F1, Np, b.flags,
-                       d.zoff);
     if (F0 && inverses) launch_factor_inverses(d, b, A0, A1, count, s, F0, F1, H0, H1);
 }
 
