@@ -208,6 +208,7 @@ __device__ __forceinline__ bool eliminate_block(PanelShared &sh, int J) {
 #pragma unroll
     for (int c = 0; c < 16; ++c) a[c] = T[r][c];
     bool ok = true;
+    double diag = 0.0;                               // L_rr
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
         double piv = bcast(a[j].x, j);
@@ -218,29 +219,35 @@ __device__ __forceinline__ bool eliminate_block(PanelShared &sh, int J) {
         double dinv = __builtin_amdgcn_rsq(piv);
         dinv = dinv * fma(-0.5 * piv * dinv, dinv, 1.5);
         dinv = dinv * fma(-0.5 * piv * dinv, dinv, 1.5);
-        a[j] = cscale(a[j], dinv);
-        sh.dinv[16 * J + j] = dinv;
+        // the updates take a_rj conj(a_cj) / piv, so that they do not wait for
+        // (nor carry the rounding of) the scaled column
+        const double2 u = cscale(a[j], dinv * dinv);
 #pragma unroll
         for (int c = j + 1; c < 16; ++c) {
             const double lx = bcast(a[j].x, c), ly = bcast(a[j].y, c);
-            // a_rc -= l_rj conj(l_cj)
-            a[c].x = fma(-a[j].y, ly, fma(-a[j].x, lx, a[c].x));
-            a[c].y = fma(a[j].x, ly, fma(-a[j].y, lx, a[c].y));
+            a[c].x = fma(-u.y, ly, fma(-u.x, lx, a[c].x));
+            a[c].y = fma(u.x, ly, fma(-u.y, lx, a[c].y));
         }
+        // L_jj = piv y, and the reciprocal of that very number, which the
+        // inverses use as well
+        const double d = piv * dinv;
+        dinv = fma(dinv, fma(-d, dinv, 1.0), dinv);
+        a[j] = cscale(a[j], dinv);
+        sh.dinv[16 * J + j] = dinv;
+        diag = r == j ? d : diag;
     }
     // the diagonal tile: zero above the diagonal, the diagonal real
     const int top = I == J ? r : 16;
     if (mine)
 #pragma unroll
         for (int c = 0; c < 16; ++c)
-            T[r][c] = make_double2(c > top ? 0.0 : a[c].x, c >= top ? 0.0 : a[c].y);
+            T[r][c] = make_double2(c > top ? 0.0 : c == top ? diag : a[c].x, c >= top ? 0.0 : a[c].y);
     return ok;
 }
 
 // Inverse of the diagonal tile J by one wave, lane = row: with
 // y_r = e_r - sum_{k<r} L_rk x_k, row r of the inverse is x_r = y_r / L_rr; step
-// j takes row j's y by readlane and subtracts (L_rj / L_jj) y_j from the rows
-// below it.
+// j takes row j's y by readlane and subtracts L_rj x_j from the rows below it.
 __device__ __forceinline__ void invert_tile(PanelShared &sh, int J) {
     const int lane = threadIdx.x & 63, r = lane & 15;
     const Tile &T = sh.L[tile_of(J, J)];
@@ -248,18 +255,19 @@ __device__ __forceinline__ void invert_tile(PanelShared &sh, int J) {
 #pragma unroll
     for (int c = 0; c < 16; ++c) {
         const double2 x = T[r][c];                   // zero above the diagonal
-        const double d = sh.dinv[16 * J + c];
-        l[c] = make_double2(c == r ? 0.0 : x.x * d, x.y * d);
+        l[c] = make_double2(c == r ? 0.0 : x.x, x.y);
         y[c] = make_double2(c == r ? 1.0 : 0.0, 0.0);
     }
 #pragma unroll
-    for (int j = 0; j < 15; ++j)
+    for (int j = 0; j < 15; ++j) {
+        const double d = sh.dinv[16 * J + j];
 #pragma unroll
         for (int c = 0; c <= j; ++c) {
-            const double px = bcast(y[c].x, j), py = bcast(y[c].y, j);
+            const double px = bcast(y[c].x, j) * d, py = bcast(y[c].y, j) * d;
             y[c].x = fma(l[j].y, py, fma(-l[j].x, px, y[c].x));
             y[c].y = fma(-l[j].y, px, fma(-l[j].x, py, y[c].y));
         }
+    }
     const double d = sh.dinv[16 * J + r];
     if (lane < 16)
 #pragma unroll
