@@ -61,6 +61,7 @@ Bufs carve(const icwf_config &c, char *base, size_t *total) {
     b.Cacc = L.take<double2>(Np);
     b.Cstage = L.take<double2>(Np);
     b.y = L.take<double2>(Np);
+    b.res = L.take<double2>(Np);
     b.rhs = L.take<double2>(Np);
     b.vphase_r = L.take<double2>(nr);
     b.vphase_R = L.take<double2>(nR);
@@ -103,8 +104,9 @@ Bufs carve(const icwf_config &c, char *base, size_t *total) {
         b.zvec = L.take<double2>(nn > 1 ? Np : 1);
     }
     b.chol_diag = L.take<double2>(2 * icwf::kCholNb * icwf::kCholNb);
+    b.ysol = L.take<double2>(Np);
     b.xsol = L.take<double2>(Np);
-    b.solve_sync = L.take<int32_t>(130);
+    b.solve_sync = L.take<int32_t>(2);
     b.bo = L.take<double>(std::max<size_t>(1, nR * nbo * nr));
     b.obs_psi = L.take<double2>(nr * nR);
     b.obs_chi = L.take<double2>(std::max<size_t>(1, nbo * nR));
@@ -702,6 +704,7 @@ icwf_status icwf_create(const icwf_config *cfg, const double *r0, const double *
         icwf::launch_cholesky(d, b, b.L[0], b.L[0], b.Linv[0], b.Linv[0], 1, st, b.Finv[0], nullptr, b.Hinv[0], nullptr);
     else
         icwf::launch_cholesky(d, b, b.L[0], b.L[0], b.Linv[0], b.Linv[0], 1, st);
+    icwf::launch_solve_reset(d, b, st);
     if (!C0) icwf::launch_solve_initial(d, b, 0, b.Cstage, st);
     CREATE_HIP(hipGetLastError());
     const icwf_status ds = device_status(s);

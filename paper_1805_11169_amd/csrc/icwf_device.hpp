@@ -93,6 +93,23 @@ __device__ inline int mfma_row_f32(int lane, int v) { return 4 * (lane >> 4) + v
 __device__ inline int mfma_row(double, int lane, int v) { return mfma_row_f64(lane, v); }
 __device__ inline int mfma_row(float, int lane, int v) { return mfma_row_f32(lane, v); }
 
+// Sum over the 16 lanes of a row of a double held by each lane (DPP
+// rotations within the row); every lane of the row ends with the sum, lane
+// 16 r in a fixed order.
+template <int CTRL>
+__device__ inline double dpp_rot(double x) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+__device__ inline double row16_sum(double x) {
+    x += dpp_rot<0x128>(x);   // row_ror:8
+    x += dpp_rot<0x124>(x);   // row_ror:4
+    x += dpp_rot<0x122>(x);   // row_ror:2
+    x += dpp_rot<0x121>(x);   // row_ror:1
+    return x;
+}
+
 // Batched launches (several simulations of one shape in one launch): the
 // simulation blockIdx.z (the outer part of it where z has another use) finds
 // every buffer at the address of the launch's first simulation plus
@@ -112,23 +129,5 @@ __device__ inline T *zshift(T *p, long long o) {
 // Device status flags (one int32 each, in the workspace).
 enum Flag : int32_t { kFlagHalt = 0, kFlagNode = 1, kFlagSolve = 2, kFlagNonfinite = 3, kFlagOut = 4,
                       kFlagHang = 5, kNumFlags = 8 };
-
-// Bounded wait of one thread for an int32 flag written by another
-// work-group (agent-scope acquire).  Every wait ends: after ~2^22 polls it
-// raises kFlagHang and kFlagHalt and returns false, and the caller goes on
-// with whatever is in memory (the host then reports the error).
-__device__ inline bool wait_flag(const int32_t *flag, int32_t *status) {
-    for (int it = 0; it < (1 << 22); ++it) {
-        if (__hip_atomic_load(flag, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) != 0) return true;
-        __builtin_amdgcn_s_sleep(2);
-    }
-    atomicOr(&status[kFlagHang], 1);
-    atomicOr(&status[kFlagHalt], 1);
-    return false;
-}
-
-__device__ inline void set_flag(int32_t *flag) {
-    __hip_atomic_store(flag, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 }  // namespace icwf

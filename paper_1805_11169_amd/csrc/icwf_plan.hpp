@@ -66,7 +66,8 @@ struct Bufs {
     double2 *psi1, *psi2;                 // [N][nr], [N][nR] CWFs (Eq. 7)
     double *r, *R, *r_new, *R_new;        // trajectory positions at t_k and t_k+1
     double2 *C, *Cacc, *Cstage;           // coefficients and RK4 stage vectors
-    double2 *y;                           // forward-substitution result of an RK stage
+    double2 *y;                           // first solution of an RK stage through the explicit inverses
+    double2 *res;                         // and its residual
     double2 *rhs;                         // K v of an RK stage
     double2 *vphase_r, *vphase_R;         // exp(-i V_1(r_i) dt/2), exp(-i V_2(R_j) dt/2)
     double2 *kin_r, *kin_R;               // exp(-i k^2 dt / 2m) / n, FFT order
@@ -100,8 +101,9 @@ struct Bufs {
     double2 *Tinv[2];                     // [Np][Np] scratch of the block inversion (sinv only)
     double2 *zvec;                        // [Np] L^-1 v of an RK stage (sinv only)
     double2 *chol_diag;                   // [2][64][64] factored diagonal blocks in flight
-    double2 *xsol;                        // [Np] back-substitution result of an RK stage
-    int32_t *solve_sync;                  // [130] block flags and tickets of the stage solves
+    double2 *ysol, *xsol;                 // [Np] forward and back-substitution results of an RK stage,
+                                          // pending between uses (launch_solve_reset)
+    int32_t *solve_sync;                  // [2] tickets of the stage solves
     double *bo;                           // [nR][n_bo][nr] BO states
     double2 *obs_psi;                     // [nr][nR] Psi on the grid (observables)
     double2 *obs_chi;                     // [n_bo][nR]
@@ -222,6 +224,9 @@ void launch_rk4(const Dims &d, const Bufs &b, int parity, hipStream_t s);
 
 // C = (L L^H)^-1 rhs with L = b.L[parity] (initial coefficients).
 void launch_solve_initial(const Dims &d, const Bufs &b, int parity, double2 *rhs, hipStream_t s);
+
+// The stage solves' hand-off words, before their first use.
+void launch_solve_reset(const Dims &d, const Bufs &b, hipStream_t s);
 
 // Copy x_k+1 -> x_k (end of a step).
 void launch_commit_positions(const Dims &d, const Bufs &b, hipStream_t s);

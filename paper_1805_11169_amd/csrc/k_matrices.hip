@@ -269,23 +269,6 @@ struct WcChunk {
 
 typedef __attribute__((address_space(3))) void lds_void;
 
-// Sum over the 16 lanes of a row of a double held by each lane (DPP
-// rotations within the row); every lane of the row ends with the sum, lane
-// 16 r in a fixed order.
-template <int CTRL>
-__device__ inline double dpp_rot(double x) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, false);
-    return __hiloint2double(hi, lo);
-}
-__device__ inline double row16_sum(double x) {
-    x += dpp_rot<0x128>(x);   // row_ror:8
-    x += dpp_rot<0x124>(x);   // row_ror:4
-    x += dpp_rot<0x122>(x);   // row_ror:2
-    x += dpp_rot<0x121>(x);   // row_ror:1
-    return x;
-}
-
 template <typename T, bool BATCHED>
 __global__ void __launch_bounds__(256, 2) k_wc(const typename WcTraits<T>::cplx *__restrict__ psi1,
                                                const double2 *__restrict__ psi2,

@@ -17,12 +17,11 @@
 // matrix cores.  A pivot that is not positive raises the solve flag.
 //
 // RK4 (classical, S and K linear in time between the step ends, so the
-// midpoint is their average).  Each stage is a matvec K v over many
-// work-groups and two launches over the 64-row blocks of the factor.
-// k_rk_fwd: a work-group solves L y = K v for its block after the blocks
-// above it are done (it waits on their flags and subtracts their
-// contributions as they arrive), then applies the inverse of its diagonal
-// block (from k_chol_panel).
+// midpoint is their average).  Each stage is two launches over the 64-row
+// blocks of the factor.  k_rk_fwd: a work-group takes its rows of K v, solves
+// L y = K v for its block after the blocks above it are done (it subtracts
+// their contributions as they arrive), then applies the inverse of its
+// diagonal block (from k_chol_panel).
 // k_rk_bwd: the same for L^H x = y from the bottom up, then the stage update
 // k = -i x of its rows.  Work-groups take blocks in ticket order, so a
 // work-group only ever waits on work-groups that are already running, and
@@ -595,11 +594,16 @@ __global__ void __launch_bounds__(256, 2) k_cgemm(GemmBatch g, const int32_t *__
 }
 
 // ------------------------------------------------------------------ RK4 stage solves
-// Synchronisation words in the workspace (int32): [0, 64) forward block
-// flags, [64, 128) backward block flags, [128] forward ticket, [129] backward
-// ticket.  Each kernel clears the other kernel's words for its next launch.
-constexpr int kMaxBlocks = 64;
-constexpr int kSyncFwd = 0, kSyncBwd = 64, kSyncTicketF = 128, kSyncTicketB = 129;
+// Blocks hand their part of y (forward) and x (backward) on through memory
+// itself: every entry holds kPending until its block writes it, and whoever
+// needs it reads it until it holds something else, so a hand-off is one store
+// and one load (with a flag beside the data: a store, a fence, a flag, and a
+// load of each; the step's four stages, N = 250: 172 -> 108 us, N = 500: 326 ->
+// 195 us, N = 1500: 1.09 -> 0.66 ms, K v taken into the forward kernel).  k_rk_bwd puts kPending back into the y it has read,
+// k_rk_fwd into the x of the stage before; the words start so at create.
+// solve_sync: the two tickets, each kernel clearing the other's.
+constexpr unsigned long long kPending = 0x7ff8dead00c0ffeeull;   // a NaN no arithmetic produces
+constexpr int kSyncTicketF = 0, kSyncTicketB = 1;
 
 __device__ inline int take_ticket(int32_t *ctr, int *slot) {
     if (threadIdx.x == 0) *slot = atomicAdd(ctr, 1);
@@ -607,19 +611,33 @@ __device__ inline int take_ticket(int32_t *ctr, int *slot) {
     return *slot;
 }
 
-// Wait (thread 0, bounded) for a block flag, then let every wave acquire it.
-__device__ inline void wait_block(const int32_t *flag, int32_t *status) {
-    if (threadIdx.x == 0) wait_flag(flag, status);
-    __syncthreads();
-    (void)__hip_atomic_load(flag, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+__device__ inline unsigned long long peek(const double *p) {
+    return __hip_atomic_load(reinterpret_cast<const unsigned long long *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-
-__device__ inline void publish_block(int32_t *flag) {
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __threadfence();
-        set_flag(flag);
+__device__ inline void post(double *p, unsigned long long v) {
+    __hip_atomic_store(reinterpret_cast<unsigned long long *>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void post(double2 *p, double2 v) {
+    post(&p->x, (unsigned long long)__double_as_longlong(v.x));
+    post(&p->y, (unsigned long long)__double_as_longlong(v.y));
+}
+__device__ inline void post_pending(double2 *p) {
+    post(&p->x, kPending);
+    post(&p->y, kPending);
+}
+// The value at p once it is there (`seen`: what a first look gave).  Bounded:
+// after ~2^20 looks it raises the flags and returns 0.
+__device__ inline double await(const double *p, unsigned long long seen, int32_t *status) {
+    for (int it = 0; seen == kPending && it < (1 << 20); ++it) {
+        __builtin_amdgcn_s_sleep(1);
+        seen = peek(p);
     }
+    if (seen == kPending) {
+        atomicOr(&status[kFlagHang], 1);
+        atomicOr(&status[kFlagHalt], 1);
+        return 0.0;
+    }
+    return __longlong_as_double((long long)seen);
 }
 
 // Parts of a matrix a matrix-vector product reads: all of it, the lower
@@ -666,62 +684,80 @@ __global__ void __launch_bounds__(256) k_matvec(const double2 *__restrict__ M, c
 }
 
 // Forward stage kernel: y_B = L_BB^-1 (rhs_B - sum_{C<B} L_BC y_C), with
-// L_BB^-1 from k_chol_panel.  256 threads; thread t: row i = t / 4 of the block,
-// quarter q = t % 4 of the columns.  Everything that does not depend on the
-// blocks above (the block's slices of L and of L_BB^-1) is loaded before the
-// waits.
-__global__ void __launch_bounds__(256) k_rk_fwd(const double2 *__restrict__ rhs, const double2 *__restrict__ L,
+// L_BB^-1 from k_chol_panel and rhs = K v (K == nullptr: rhs as given).  256
+// threads; thread t: row i = t / 4 of the block, columns 4 c + q, q = t % 4.
+// Everything that does not depend on the blocks above (rhs_B, the block's
+// slices of L and of L_BB^-1) is loaded before the waits.
+__global__ void __launch_bounds__(256) k_rk_fwd(const double2 *__restrict__ K, const double2 *__restrict__ v,
+                                                const double2 *__restrict__ rhs, const double2 *__restrict__ L,
                                                 const double2 *__restrict__ Linv, double2 *__restrict__ ybuf,
-                                                int Np, int32_t *__restrict__ sync, int32_t *__restrict__ flags, const long long *__restrict__ zoff) {
+                                                double2 *__restrict__ xbuf, int Np, int32_t *__restrict__ sync,
+                                                int32_t *__restrict__ flags, const long long *__restrict__ zoff) {
     const long long zo_ = batch_offset(zoff);
+    K = zshift(K, zo_);
+    v = zshift(v, zo_);
     rhs = zshift(rhs, zo_);
     L = zshift(L, zo_);
     Linv = zshift(Linv, zo_);
     ybuf = zshift(ybuf, zo_);
+    xbuf = zshift(xbuf, zo_);
     sync = zshift(sync, zo_);
     flags = zshift(flags, zo_);
 
-    __shared__ double2 uvec[NB];
+    __shared__ double2 yc[2][NB], uvec[NB];
     __shared__ int slot;
     const int B = take_ticket(&sync[kSyncTicketF], &slot);
-    if (B == 0) {
-        for (int e = threadIdx.x; e < kMaxBlocks; e += 256) sync[kSyncBwd + e] = 0;
-        if (threadIdx.x == 0) sync[kSyncTicketB] = 0;
-    }
+    if (B == 0 && threadIdx.x == 0) sync[kSyncTicketB] = 0;
     const bool halted = flags[kFlagHalt] != 0;
     const int t = threadIdx.x, i = t >> 2, q = t & 3;
     const int r0 = B * NB;
-    double2 iv[16];   // row i of L_BB^-1, columns 16 q ..
+    if (t < NB) post_pending(&xbuf[r0 + t]);
+    if (halted) {                                    // nobody waits for ever
+        if (t < NB) post(&ybuf[r0 + t], make_double2(0, 0));
+        return;
+    }
+    double2 iv[16];   // row i of L_BB^-1
 #pragma unroll
-    for (int c = 0; c < 16; ++c) iv[c] = halted ? make_double2(0, 0) : Linv[(size_t)(r0 + i) * NB + 16 * q + c];
-    // contributions of the blocks above, as they complete
+    for (int c = 0; c < 16; ++c) iv[c] = Linv[(size_t)(r0 + i) * NB + 4 * c + q];
     double2 part = make_double2(0, 0);
+    if (K) {
+        // minus row i of K v
+        const double2 *krow = K + (size_t)(r0 + i) * Np + q;
+#pragma unroll 8
+        for (int c = 0; c < Np / 4; ++c) part = csub(part, cmul(krow[4 * c], v[4 * c + q]));
+    }
+    // contributions of the blocks above, as they complete: the words of block
+    // C are awaited by the first 128 threads
+    const double *words = reinterpret_cast<const double *>(ybuf);
+    unsigned long long seen = t < 2 * NB && B > 0 ? peek(words + t) : 0;
     for (int C = 0; C < B; ++C) {
         double2 lv[16];
-        const double2 *lrow = L + (size_t)(r0 + i) * Np + C * NB + 16 * q;
+        const double2 *lrow = L + (size_t)(r0 + i) * Np + C * NB + q;
 #pragma unroll
-        for (int c = 0; c < 16; ++c) lv[c] = halted ? make_double2(0, 0) : lrow[c];
-        wait_block(&sync[kSyncFwd + C], flags);
-        if (halted) continue;
-        const double2 *yc = ybuf + C * NB + 16 * q;
+        for (int c = 0; c < 16; ++c) lv[c] = lrow[4 * c];
+        if (t < 2 * NB) {
+            const double x = await(words + (size_t)C * 2 * NB + t, seen, flags);
+            reinterpret_cast<double *>(yc[C & 1])[t] = x;
+            if (C + 1 < B) seen = peek(words + (size_t)(C + 1) * 2 * NB + t);
+        }
+        __syncthreads();
 #pragma unroll
-        for (int c = 0; c < 16; ++c) part = cadd(part, cmul(lv[c], yc[c]));
+        for (int c = 0; c < 16; ++c) part = cadd(part, cmul(lv[c], yc[C & 1][4 * c + q]));
     }
     part.x += __shfl_xor(part.x, 1);
     part.y += __shfl_xor(part.y, 1);
     part.x += __shfl_xor(part.x, 2);
     part.y += __shfl_xor(part.y, 2);
-    if (q == 0) uvec[i] = halted ? make_double2(0, 0) : csub(rhs[r0 + i], part);
+    if (q == 0) uvec[i] = K ? make_double2(-part.x, -part.y) : csub(rhs[r0 + i], part);
     __syncthreads();
     double2 y = make_double2(0, 0);
 #pragma unroll
-    for (int c = 0; c < 16; ++c) y = cadd(y, cmul(iv[c], uvec[16 * q + c]));
+    for (int c = 0; c < 16; ++c) y = cadd(y, cmul(iv[c], uvec[4 * c + q]));
     y.x += __shfl_xor(y.x, 1);
     y.y += __shfl_xor(y.y, 1);
     y.x += __shfl_xor(y.x, 2);
     y.y += __shfl_xor(y.y, 2);
-    if (!halted && q == 0) ybuf[r0 + i] = y;
-    publish_block(&sync[kSyncFwd + B]);
+    if (q == 0) post(&ybuf[r0 + i], y);
 }
 
 // The RK4 stage update of row ii from its solve x = (S + eps I)^-1 K v:
@@ -767,7 +803,7 @@ __device__ inline void stage_update(int ii, double2 u, int stage, double dt, int
 // from the bottom up; then the RK4 stage update of the block's rows.
 // stage: 1..4; 0 = initial coefficients (C = x).
 __global__ void __launch_bounds__(256) k_rk_bwd(const double2 *__restrict__ L, const double2 *__restrict__ Linv,
-                                                const double2 *__restrict__ ybuf, double2 *__restrict__ xbuf, int Np,
+                                                double2 *__restrict__ ybuf, double2 *__restrict__ xbuf, int Np,
                                                 int nblk, int stage, double dt, int N, double2 *__restrict__ C,
                                                 double2 *__restrict__ Cacc, double2 *__restrict__ Cstage,
                                                 double *__restrict__ r, double *__restrict__ R,
@@ -788,51 +824,149 @@ __global__ void __launch_bounds__(256) k_rk_bwd(const double2 *__restrict__ L, c
     sync = zshift(sync, zo_);
     flags = zshift(flags, zo_);
 
-    __shared__ double2 uvec[NB];
+    __shared__ double2 xc[2][NB], uvec[NB];
     __shared__ int slot;
     const int ticket = take_ticket(&sync[kSyncTicketB], &slot);
     const int B = nblk - 1 - ticket;
-    if (ticket == 0) {
-        for (int e = threadIdx.x; e < kMaxBlocks; e += 256) sync[kSyncFwd + e] = 0;
-        if (threadIdx.x == 0) sync[kSyncTicketF] = 0;
-    }
+    if (ticket == 0 && threadIdx.x == 0) sync[kSyncTicketF] = 0;
     const bool halted = flags[kFlagHalt] != 0;
     const int t = threadIdx.x, i = t >> 2, q = t & 3;
     const int r0 = B * NB;
-    double2 iv[16];   // column i of L_BB^-1, rows 16 q ..
+    double2 yb = make_double2(0, 0);
+    if (q == 0) {
+        yb = ybuf[r0 + i];
+        post_pending(&ybuf[r0 + i]);
+    }
+    if (halted) {                                    // nobody waits for ever
+        if (q == 0) post(&xbuf[r0 + i], make_double2(0, 0));
+        return;
+    }
+    double2 iv[16];   // column i of L_BB^-1
 #pragma unroll
-    for (int c = 0; c < 16; ++c) iv[c] = halted ? make_double2(0, 0) : Linv[(size_t)(r0 + 16 * q + c) * NB + i];
+    for (int c = 0; c < 16; ++c) iv[c] = Linv[(size_t)(r0 + 4 * c + q) * NB + i];
     // contributions of the blocks below (already solved): sum_k conj(L[C64+k][B64+i]) x[C64+k]
     double2 part = make_double2(0, 0);
+    const double *words = reinterpret_cast<const double *>(xbuf);
+    unsigned long long seen = t < 2 * NB && B < nblk - 1 ? peek(words + (size_t)(nblk - 1) * 2 * NB + t) : 0;
     for (int Cb = nblk - 1; Cb > B; --Cb) {
         double2 lv[16];
-        const double2 *lcol = L + (size_t)(Cb * NB + 16 * q) * Np + r0 + i;
+        const double2 *lcol = L + (size_t)(Cb * NB + q) * Np + r0 + i;
 #pragma unroll
-        for (int c = 0; c < 16; ++c) lv[c] = halted ? make_double2(0, 0) : lcol[(size_t)c * Np];
-        wait_block(&sync[kSyncBwd + Cb], flags);
-        if (halted) continue;
-        const double2 *xc = xbuf + Cb * NB + 16 * q;
+        for (int c = 0; c < 16; ++c) lv[c] = lcol[(size_t)(4 * c) * Np];
+        if (t < 2 * NB) {
+            const double x = await(words + (size_t)Cb * 2 * NB + t, seen, flags);
+            reinterpret_cast<double *>(xc[Cb & 1])[t] = x;
+            if (Cb - 1 > B) seen = peek(words + (size_t)(Cb - 1) * 2 * NB + t);
+        }
+        __syncthreads();
 #pragma unroll
-        for (int c = 0; c < 16; ++c) part = cadd(part, cmul(cconj(lv[c]), xc[c]));
+        for (int c = 0; c < 16; ++c) part = cadd(part, cmulc(lv[c], xc[Cb & 1][4 * c + q]));
     }
     part.x += __shfl_xor(part.x, 1);
     part.y += __shfl_xor(part.y, 1);
     part.x += __shfl_xor(part.x, 2);
     part.y += __shfl_xor(part.y, 2);
-    if (q == 0) uvec[i] = halted ? make_double2(0, 0) : csub(ybuf[r0 + i], part);
+    if (q == 0) uvec[i] = csub(yb, part);
     __syncthreads();
     double2 u = make_double2(0, 0);
 #pragma unroll
-    for (int c = 0; c < 16; ++c) u = cadd(u, cmul(cconj(iv[c]), uvec[16 * q + c]));
+    for (int c = 0; c < 16; ++c) u = cadd(u, cmulc(iv[c], uvec[4 * c + q]));
     u.x += __shfl_xor(u.x, 1);
     u.y += __shfl_xor(u.y, 1);
     u.x += __shfl_xor(u.x, 2);
     u.y += __shfl_xor(u.y, 2);
-    if (!halted && q == 0) {
-        xbuf[r0 + i] = u;
+    if (q == 0) {
+        post(&xbuf[r0 + i], u);
         stage_update(r0 + i, u, stage, dt, N, C, Cacc, Cstage, r, R, r_new, R_new, flags);
     }
-    publish_block(&sync[kSyncBwd + B]);
+}
+
+// The four stages of one block (N <= 64) in one work-group of 16 waves: no
+// launch between them.  Thread t has row t / 16 of K, L^-1 and L^-H, columns
+// t % 16 + 16 m, so a product is four terms per thread and a sum over the 16
+// lanes of a DPP row; L^-H comes from L^-1 through LDS.  The next stage's
+// matrices are requested before this stage's sums.  Latency-bound: 14 us for
+// the step's four stages against 53 in twelve launches (41 with rows summed
+// over 64 lanes by shuffles, which fill the LDS pipe).
+constexpr int kSoloWaves = 16;
+
+struct SoloArgs {
+    const double2 *K[4], *X[4];
+    double2 *C;
+    double *r, *R;
+    const double *r_new, *R_new;
+    int32_t *flags;
+    double dt;
+    int N;
+};
+
+__global__ void __launch_bounds__(64 * kSoloWaves) k_rk4_solo(SoloArgs g, const long long *__restrict__ zoff) {
+    const long long zo_ = batch_offset(zoff);
+    int32_t *flags = zshift(g.flags, zo_);
+    if (flags[kFlagHalt]) return;
+    __shared__ double2 tr[NB][NB + 1];               // L^-1 on its way to L^-H
+    __shared__ double2 v[NB], w[NB], y[NB], sol[NB]; // the stage's vector, K v, L^-1 K v, the solution
+    const int t = threadIdx.x, row = t >> 4, c = t & 15;
+    double2 *C = zshift(g.C, zo_);
+    double2 k[2][4], x[2][4], h[4];
+    auto load = [&](int s) __attribute__((always_inline)) {
+        const double2 *K = zshift(g.K[s], zo_) + row * NB + c, *X = zshift(g.X[s], zo_) + row * NB + c;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            k[s & 1][m] = K[16 * m];
+            x[s & 1][m] = X[16 * m];
+        }
+    };
+    // row `row` of M u, on the 16 lanes of the row
+    auto times = [&](const double2 (&a)[4], const double2 *u) __attribute__((always_inline)) {
+        double2 p = cmul(a[0], u[c]);
+#pragma unroll
+        for (int m = 1; m < 4; ++m) p = cadd(p, cmul(a[m], u[c + 16 * m]));
+        return make_double2(row16_sum(p.x), row16_sum(p.y));
+    };
+    load(0);
+    double2 c0 = make_double2(0, 0), acc = c0;
+    if (t < NB) {
+        c0 = C[t];
+        v[t] = c0;
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        if (s < 3) load(s + 1);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) tr[row][c + 16 * m] = x[s & 1][m];
+        __syncthreads();
+        double2 p = times(k[s & 1], v);
+        if (c == 0) w[row] = p;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) h[m] = cconj(tr[c + 16 * m][row]);
+        __syncthreads();
+        p = times(x[s & 1], w);
+        if (c == 0) y[row] = p;
+        __syncthreads();
+        p = times(h, y);
+        if (c == 0) sol[row] = p;
+        __syncthreads();
+        if (t < NB) {
+            // k = -i x and the stage update, as stage_update
+            const double2 u = sol[t], kk = make_double2(u.y, -u.x);
+            if (s < 3) {
+                acc = s == 0 ? kk : cadd(acc, cscale(kk, 2.0));
+                v[t] = cadd(c0, cscale(kk, s < 2 ? 0.5 * g.dt : g.dt));
+            } else {
+                const double2 cn = cadd(c0, cscale(cadd(acc, kk), g.dt / 6.0));
+                C[t] = cn;
+                if (!(isfinite(cn.x) && isfinite(cn.y))) {
+                    atomicOr(&flags[kFlagNonfinite], 1);
+                    atomicOr(&flags[kFlagHalt], 1);
+                }
+                if (t < g.N && g.r) {                // r == nullptr: Heun trajectories, positions set by the corrector
+                    zshift(g.r, zo_)[t] = zshift(g.r_new, zo_)[t];
+                    zshift(g.R, zo_)[t] = zshift(g.R_new, zo_)[t];
+                }
+            }
+        }
+    }
 }
 
 // Stages through the explicit inverse of the factor, A^-1 = L^-H L^-1, with
@@ -924,6 +1058,11 @@ __global__ void k_set_table(long long *__restrict__ tab, BatchTable t, int n) {
     if ((int)threadIdx.x < n) tab[threadIdx.x] = t.off[threadIdx.x];
 }
 
+__global__ void k_fill_u64(unsigned long long *p, int n, unsigned long long v) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = v;
+}
+
 __global__ void k_fill_i32(int32_t *p, int n, int32_t v, const long long *__restrict__ zoff) {
     const long long zo_ = batch_offset(zoff);
     p = zshift(p, zo_);
@@ -1010,11 +1149,28 @@ void launch_rk4(const Dims &d, const Bufs &b, int parity, hipStream_t s) {
     const double2 *Hs[4] = {b.Hinv[cur], b.Hinvmid, b.Hinvmid, b.Hinv[nxt]};
     // with Heun trajectories the last stage leaves x_k in place for the corrector
     double *cr = d.traj == 1 ? nullptr : b.r, *cR = d.traj == 1 ? nullptr : b.R;
+    if (!d.sinv && nblk == 1) {
+        SoloArgs g{};
+        for (int st = 0; st < 4; ++st) {
+            g.K[st] = Ks[st];
+            g.X[st] = Xs[st];
+        }
+        g.C = b.C;
+        g.r = cr;
+        g.R = cR;
+        g.r_new = b.r_new;
+        g.R_new = b.R_new;
+        g.flags = b.flags;
+        g.dt = d.dt;
+        g.N = d.N;
+        hipLaunchKernelGGL(k_rk4_solo, dim3(1, 1, d.batch), dim3(64 * kSoloWaves), 0, s, g, d.zoff);
+        return;
+    }
     for (int st = 1; st <= 4; ++st) {
         const double2 *v = (st == 1) ? b.C : b.Cstage;
-        hipLaunchKernelGGL(k_matvec, dim3(Np, 1, d.batch), dim3(256), 0, s, Ks[st - 1], v, b.rhs, Np,
-                           (int)kPartAll, b.flags, d.zoff);
         if (d.sinv) {
+            hipLaunchKernelGGL(k_matvec, dim3(Np, 1, d.batch), dim3(256), 0, s, Ks[st - 1], v, b.rhs, Np,
+                               (int)kPartAll, b.flags, d.zoff);
             // A of the stage: S_k + eps I, the midpoint average + eps I (stages 2, 3), S_k+1 + eps I
             const double2 *Sa = st == 4 ? b.Smat[nxt] : b.Smat[cur];
             const double2 *Sb = (st == 2 || st == 3) ? b.Smat[nxt] : nullptr;
@@ -1022,28 +1178,36 @@ void launch_rk4(const Dims &d, const Bufs &b, int parity, hipStream_t s) {
                                (int)kPartLower, b.flags, d.zoff);
             hipLaunchKernelGGL(k_matvec, dim3(Np, 1, d.batch), dim3(256), 0, s, Hs[st - 1], b.zvec, b.y, Np,
                                (int)kPartUpper, b.flags, d.zoff);
-            hipLaunchKernelGGL(k_rk_resid, dim3(Np, 1, d.batch), dim3(256), 0, s, Sa, Sb, d.eps, b.y, b.rhs, b.xsol,
+            hipLaunchKernelGGL(k_rk_resid, dim3(Np, 1, d.batch), dim3(256), 0, s, Sa, Sb, d.eps, b.y, b.rhs, b.res,
                                Np, b.flags, d.zoff);
-            hipLaunchKernelGGL(k_matvec, dim3(Np, 1, d.batch), dim3(256), 0, s, Fs[st - 1], b.xsol, b.zvec, Np,
+            hipLaunchKernelGGL(k_matvec, dim3(Np, 1, d.batch), dim3(256), 0, s, Fs[st - 1], b.res, b.zvec, Np,
                                (int)kPartLower, b.flags, d.zoff);
             hipLaunchKernelGGL(k_rk_apply, dim3(Np, 1, d.batch), dim3(256), 0, s, Hs[st - 1], b.zvec, b.y, Np, st,
                                d.dt, d.N, b.C, b.Cacc, b.Cstage, cr, cR, b.r_new, b.R_new, b.flags, d.zoff);
             continue;
         }
-        hipLaunchKernelGGL(k_rk_fwd, dim3(nblk, 1, d.batch), dim3(256), 0, s, b.rhs, Ls[st - 1], Xs[st - 1], b.y, Np,
-                           b.solve_sync, b.flags, d.zoff);
-        hipLaunchKernelGGL(k_rk_bwd, dim3(nblk, 1, d.batch), dim3(256), 0, s, Ls[st - 1], Xs[st - 1], b.y, b.xsol, Np,
-                           nblk, st, d.dt, d.N, b.C, b.Cacc, b.Cstage, cr, cR, b.r_new, b.R_new, b.solve_sync, b.flags,
+        hipLaunchKernelGGL(k_rk_fwd, dim3(nblk, 1, d.batch), dim3(256), 0, s, Ks[st - 1], v, nullptr, Ls[st - 1],
+                           Xs[st - 1], b.ysol, b.xsol, Np, b.solve_sync, b.flags, d.zoff);
+        hipLaunchKernelGGL(k_rk_bwd, dim3(nblk, 1, d.batch), dim3(256), 0, s, Ls[st - 1], Xs[st - 1], b.ysol, b.xsol,
+                           Np, nblk, st, d.dt, d.N, b.C, b.Cacc, b.Cstage, cr, cR, b.r_new, b.R_new, b.solve_sync, b.flags,
                            d.zoff);
     }
 }
 
 void launch_solve_initial(const Dims &d, const Bufs &b, int parity, double2 *rhs, hipStream_t s) {
     const int Np = padded(d.N), nblk = Np / NB;
-    hipLaunchKernelGGL(k_rk_fwd, dim3(nblk), dim3(256), 0, s, rhs, b.L[parity], b.Linv[parity], b.y, Np,
-                       b.solve_sync, b.flags, nullptr);
-    hipLaunchKernelGGL(k_rk_bwd, dim3(nblk), dim3(256), 0, s, b.L[parity], b.Linv[parity], b.y, b.xsol, Np, nblk, 0,
+    hipLaunchKernelGGL(k_rk_fwd, dim3(nblk), dim3(256), 0, s, nullptr, nullptr, rhs, b.L[parity], b.Linv[parity],
+                       b.ysol, b.xsol, Np, b.solve_sync, b.flags, nullptr);
+    hipLaunchKernelGGL(k_rk_bwd, dim3(nblk), dim3(256), 0, s, b.L[parity], b.Linv[parity], b.ysol, b.xsol, Np, nblk, 0,
                        d.dt, d.N, b.C, b.Cacc, b.Cstage, b.r, b.R, b.r_new, b.R_new, b.solve_sync, b.flags, nullptr);
+}
+
+void launch_solve_reset(const Dims &d, const Bufs &b, hipStream_t s) {
+    const int Np = padded(d.N);
+    hipLaunchKernelGGL(k_fill_u64, dim3((2 * Np + 255) / 256), dim3(256), 0, s,
+                       reinterpret_cast<unsigned long long *>(b.ysol), 2 * Np, kPending);
+    hipLaunchKernelGGL(k_fill_u64, dim3((2 * Np + 255) / 256), dim3(256), 0, s,
+                       reinterpret_cast<unsigned long long *>(b.xsol), 2 * Np, kPending);
 }
 
 void launch_set_table(long long *tab, const BatchTable &t, int n, hipStream_t s) {
