@@ -110,6 +110,20 @@ __device__ inline double row16_sum(double x) {
     return x;
 }
 
+typedef double dbl2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(1))) char gchar;
+typedef __attribute__((address_space(1))) dbl2 gdouble2;
+
+// A wave-uniform global address whose origin the compiler cannot see, and a
+// point that loads through it are not moved across: without the two it sinks
+// the loads of the next step down to their use.
+__device__ __forceinline__ const gchar *opaque(const void *p) {
+    uint64_t u = reinterpret_cast<uint64_t>(p);
+    asm volatile("" : "+s"(u));
+    return reinterpret_cast<const gchar *>(u);
+}
+__device__ __forceinline__ void pin_loads() { asm volatile("" ::: "memory"); }
+
 // Batched launches (several simulations of one shape in one launch): the
 // simulation blockIdx.z (the outer part of it where z has another use) finds
 // every buffer at the address of the launch's first simulation plus

@@ -35,36 +35,38 @@ __device__ inline flt4 mfma(float a, float b, flt4 c) {
 }
 
 // ---------------------------------------------------------------- conditioned kets
-__global__ void k_cond_kets(const double2 *__restrict__ psi, int n, double x_min, double h,
-                            const double *__restrict__ cond_a, const double *__restrict__ cond_b, int species,
-                            ModelParams mp, double2 *__restrict__ Ga, double2 *__restrict__ Gb, int Np,
-                            const int32_t *__restrict__ flags, const long long *__restrict__ zoff, const ModelParams *__restrict__ mpd) {
+// Both species in one launch: the first `blocks1` work-groups species 1.
+struct CondSpecies {
+    const double2 *psi;
+    const double *cond_a, *cond_b;
+    double2 *Ga, *Gb;
+    int n;
+    double x_min, h;
+};
+
+__global__ void k_cond_kets(CondSpecies s1, CondSpecies s2, unsigned blocks1, ModelParams mp, int Np,
+                            const int32_t *__restrict__ flags, const long long *__restrict__ zoff,
+                            const ModelParams *__restrict__ mpd) {
     const long long zo_ = batch_offset(zoff);
-    psi = zshift(psi, zo_);
-    cond_a = zshift(cond_a, zo_);
-    cond_b = zshift(cond_b, zo_);
-    Ga = zshift(Ga, zo_);
-    Gb = zshift(Gb, zo_);
     flags = zshift(flags, zo_);
     if (zoff) mp = *zshift(mpd, zo_);
 
     if (flags[kFlagHalt]) return;
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (size_t)Np * n) return;
-    const int a = (int)(idx / n);
-    const int i = (int)(idx - (size_t)a * n);
-    const double x = x_min + i * h;
-    const double2 p = psi[idx];
-    double wa, wb;
-    if (species == 1) {
-        wa = model_wc(mp, x, cond_a[a]);
-        wb = model_wc(mp, x, cond_b[a]);
-    } else {
-        wa = model_wc(mp, cond_a[a], x);
-        wb = model_wc(mp, cond_b[a], x);
+    const bool first = blockIdx.x < blocks1;
+    const CondSpecies &c = first ? s1 : s2;
+    const size_t idx = (size_t)(first ? blockIdx.x : blockIdx.x - blocks1) * blockDim.x + threadIdx.x;
+    if (idx >= (size_t)Np * c.n) return;
+    const int a = (int)(idx / c.n);
+    const int i = (int)(idx - (size_t)a * c.n);
+    const double x = c.x_min + i * c.h;
+    const double2 p = zshift(c.psi, zo_)[idx];
+    const double xa = zshift(c.cond_a, zo_)[a], xb = zshift(c.cond_b, zo_)[a];
+    const double wa = first ? model_wc(mp, x, xa) : model_wc(mp, xa, x);
+    zshift(c.Ga, zo_)[idx] = cscale(p, wa);
+    if (c.Gb) {
+        const double wb = first ? model_wc(mp, x, xb) : model_wc(mp, xb, x);
+        zshift(c.Gb, zo_)[idx] = cscale(p, wb);
     }
-    Ga[idx] = cscale(p, wa);
-    if (Gb) Gb[idx] = cscale(p, wb);
 }
 
 // ---------------------------------------------------------------- batched conj-NT complex GEMM
@@ -206,6 +208,121 @@ __global__ void __launch_bounds__(256, 2) k_zgemm(ZBatch zb, int Np, const int32
                 out[(size_t)b * Np + a] = o;
                 if (mirror) out[(size_t)a * Np + b] = cconj(o);
             }
+}
+
+// The same products where 64 x 64 tiles are too few for the device: a
+// work-group per 16 F x 16 F tile, its four waves taking the steps of the
+// reduction (16 points each) in turn, operands straight from global memory one
+// step ahead, four consecutive points per lane; the four partial tiles meet in
+// LDS.  The sums do not depend on F.
+template <int F, bool BATCHED>
+__global__ void __launch_bounds__(256, 2) k_zgemm_split(ZBatch zb, int Np, const int32_t *__restrict__ flags, int zcnt,
+                                                        const long long *__restrict__ zoff) {
+    const int sim = BATCHED ? blockIdx.z / zcnt : 0, z = blockIdx.z - sim * zcnt;
+    const long long zo_ = BATCHED ? batch_offset(zoff, sim) : 0;
+    flags = zshift(flags, zo_);
+    if (flags[kFlagHalt]) return;
+    const int bt = blockIdx.y, at = blockIdx.x;
+    const double2 *X = zshift(zpick(zb.X, z), zo_);
+    const double2 *Y = zshift(zpick(zb.Y, z), zo_);
+    const bool herm = X == Y;   // the output is Hermitian: upper tiles only
+    if (herm && bt > at) return;
+    constexpr int W = 4, T = 16 * F, EP = 4, ITEMS = 4 * F * F;
+    __shared__ double2 red[W][ITEMS][64];
+    const int K = zpick(zb.K, z);
+    const int t = threadIdx.x, lane = t & 63, row = lane & 15, quarter = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int b0 = bt * T, a0 = at * T;
+    dbl4 re[F][F], im[F][F];
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+        for (int g = 0; g < F; ++g) {
+            re[f][g] = dbl4{0, 0, 0, 0};
+            im[f][g] = dbl4{0, 0, 0, 0};
+        }
+    const int count = (K / (4 * EP) - wave + W - 1) / W;     // steps of this wave
+    if (count > 0) {
+        constexpr uint32_t kStep = 64u * EP;                 // bytes of a row per step
+        const gchar *xat = opaque(X + (size_t)b0 * K) + (size_t)wave * kStep;
+        const gchar *yat = opaque(Y + (size_t)a0 * K) + (size_t)wave * kStep;
+        const uint32_t off = (uint32_t)row * K * 16u + quarter * 16u * EP, frow = 256u * K;
+        dbl2 x[F][EP], y[F][EP];
+        auto load = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int f = 0; f < F; ++f)
+#pragma unroll
+                for (int e = 0; e < EP; ++e) {
+                    x[f][e] = *reinterpret_cast<const gdouble2 *>(xat + (size_t)f * frow + off + 16u * e);
+                    y[f][e] = *reinterpret_cast<const gdouble2 *>(yat + (size_t)f * frow + off + 16u * e);
+                }
+            pin_loads();
+        };
+        load();
+        for (int s = 0; s < count; ++s) {
+            dbl2 xc[F][EP], yc[F][EP];
+#pragma unroll
+            for (int f = 0; f < F; ++f)
+#pragma unroll
+                for (int e = 0; e < EP; ++e) {
+                    xc[f][e] = x[f][e];
+                    yc[f][e] = y[f][e];
+                }
+            const size_t st = s + 1 < count ? W * kStep : 0;  // the last step loads its own operands again (never used)
+            xat += st;
+            yat += st;
+            load();
+#pragma unroll
+            for (int e = 0; e < EP; ++e)
+#pragma unroll
+                for (int f = 0; f < F; ++f)
+#pragma unroll
+                    for (int g = 0; g < F; ++g) {
+                        // conj(x) y = (xr yr + xi yi) + i (xr yi - xi yr)
+                        re[f][g] = mfma(xc[f][e].x, yc[g][e].x, re[f][g]);
+                        im[f][g] = mfma(xc[f][e].x, yc[g][e].y, im[f][g]);
+                        re[f][g] = mfma(xc[f][e].y, yc[g][e].y, re[f][g]);
+                        im[f][g] = mfma(-xc[f][e].y, yc[g][e].x, im[f][g]);
+                    }
+        }
+    }
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+        for (int g = 0; g < F; ++g)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red[wave][(f * F + g) * 4 + v][lane] = make_double2(re[f][g][v], im[f][g][v]);
+    __syncthreads();
+    const double sc = zpick(zb.scale, z);
+    double2 *out = zshift(zpick(zb.out, z), zo_);
+#pragma unroll
+    for (int q = 0; q < ITEMS / W; ++q) {
+        const int it = q * W + wave, v = it & 3, g = (it >> 2) % F, f = (it >> 2) / F;
+        // Hermitian: by fragments of 16, so that the entries below the
+        // diagonal are the conjugates of those above it whatever F is
+        if (herm && bt * F + f > at * F + g) continue;
+        const bool mirror = herm && bt * F + f < at * F + g;
+        const double2 o = cscale(cadd(cadd(red[0][it][lane], red[1][it][lane]), cadd(red[2][it][lane], red[3][it][lane])), sc);
+        const int b = b0 + 16 * f + mfma_row_f64(lane, v), a = a0 + 16 * g + row;
+        out[(size_t)b * Np + a] = o;
+        if (mirror) out[(size_t)a * Np + b] = cconj(o);
+    }
+}
+
+// Up to 768 padded trajectories (alone or in a batch, which has to give the
+// same sums) the split kernel, on tiles of 16 while those of 32 leave compute
+// units idle.  Six products of one simulation at 512 x 256, tiles of 16, 32
+// and the 64 of k_zgemm: N = 64, 21, 30 and 83 us; N = 250, 51, 48 and 86;
+// N = 500, 164, 102 and 142; N = 1024, 287, 179 and 176.
+static void launch_zgemm(const Dims &d, const ZBatch &zb, int c, const int32_t *flags, hipStream_t s) {
+    const int Np = padded(d.N);
+    auto go = [&](auto kernel, int T) {
+        hipLaunchKernelGGL(kernel, dim3(Np / T, Np / T, c * d.batch), dim3(256), 0, s, zb, Np, flags, c, d.zoff);
+    };
+    if (Np > 768) go(d.zoff ? k_zgemm<true> : k_zgemm<false>, kZT);
+    else if ((long long)c * d.batch * (Np / 32) * (Np / 32) <= 256)
+        go(d.zoff ? k_zgemm_split<1, true> : k_zgemm_split<1, false>, 16);
+    else go(d.zoff ? k_zgemm_split<2, true> : k_zgemm_split<2, false>, 32);
 }
 
 // ---------------------------------------------------------------- two-body contraction
@@ -559,20 +676,6 @@ __global__ void __launch_bounds__(256, 2) k_wc(const typename WcTraits<T>::cplx 
 // products per 16 pair-product operations): 0.57 of the FP64 peak on 32 ranks
 // at N = 512, 512 x 256, 0.73 at 4096 x 256, where a unit's sums are longer
 // against its two reductions.
-typedef double dbl2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(1))) char gchar;
-typedef __attribute__((address_space(1))) dbl2 gdouble2;
-
-// A wave-uniform global address whose origin the compiler cannot see, and a
-// point that loads through it are not moved across: without the two it sinks
-// the loads of the next step down to their use.
-__device__ __forceinline__ const gchar *opaque(const void *p) {
-    uint64_t u = reinterpret_cast<uint64_t>(p);
-    asm volatile("" : "+s"(u));
-    return reinterpret_cast<const gchar *>(u);
-}
-__device__ __forceinline__ void pin_loads() { asm volatile("" ::: "memory"); }
-
 constexpr int kSepWaves = 4;
 
 // Operand loads of one wave's steps of one species: uniform bases plus lane
@@ -804,28 +907,24 @@ std::vector<int32_t> wc_tile_order(int Np) {
     return ord;
 }
 
-void launch_cond_kets(const Dims &d, const Bufs &b, hipStream_t s, bool next) {
+static void launch_kets(const Dims &d, const Bufs &b, const CondSpecies &s1, const CondSpecies &s2, hipStream_t s) {
     const int Np = padded(d.N);
-    size_t tot = (size_t)Np * d.nr;
-    hipLaunchKernelGGL(k_cond_kets, dim3((unsigned)((tot + 255) / 256), 1, d.batch), dim3(256), 0, s, b.psi1, d.nr,
-                       d.r_min, d.hr, b.R, b.R_new, 1, d.mp, b.G1a, next ? b.G1b : nullptr, Np, b.flags, d.zoff, d.mpd);
-    tot = (size_t)Np * d.nR;
-    hipLaunchKernelGGL(k_cond_kets, dim3((unsigned)((tot + 255) / 256), 1, d.batch), dim3(256), 0, s, b.psi2, d.nR,
-                       d.R_min, d.hR, b.r, b.r_new, 2, d.mp, b.G2a, next ? b.G2b : nullptr, Np, b.flags, d.zoff, d.mpd);
+    const unsigned blocks1 = (unsigned)(((size_t)Np * d.nr + 255) / 256), blocks2 = (unsigned)(((size_t)Np * d.nR + 255) / 256);
+    hipLaunchKernelGGL(k_cond_kets, dim3(blocks1 + blocks2, 1, d.batch), dim3(256), 0, s, s1, s2, blocks1, d.mp, Np,
+                       b.flags, d.zoff, d.mpd);
+}
+
+void launch_cond_kets(const Dims &d, const Bufs &b, hipStream_t s, bool next) {
+    launch_kets(d, b, {b.psi1, b.R, b.R_new, b.G1a, next ? b.G1b : nullptr, d.nr, d.r_min, d.hr},
+                {b.psi2, b.r, b.r_new, b.G2a, next ? b.G2b : nullptr, d.nR, d.R_min, d.hR}, s);
 }
 
 void launch_cond_kets_next(const Dims &d, const Bufs &b, hipStream_t s) {
-    const int Np = padded(d.N);
-    size_t tot = (size_t)Np * d.nr;
-    hipLaunchKernelGGL(k_cond_kets, dim3((unsigned)((tot + 255) / 256), 1, d.batch), dim3(256), 0, s, b.psi1, d.nr,
-                       d.r_min, d.hr, b.R_new, b.R_new, 1, d.mp, b.G1b, nullptr, Np, b.flags, d.zoff, d.mpd);
-    tot = (size_t)Np * d.nR;
-    hipLaunchKernelGGL(k_cond_kets, dim3((unsigned)((tot + 255) / 256), 1, d.batch), dim3(256), 0, s, b.psi2, d.nR,
-                       d.R_min, d.hR, b.r_new, b.r_new, 2, d.mp, b.G2b, nullptr, Np, b.flags, d.zoff, d.mpd);
+    launch_kets(d, b, {b.psi1, b.R_new, b.R_new, b.G1b, nullptr, d.nr, d.r_min, d.hr},
+                {b.psi2, b.r_new, b.r_new, b.G2b, nullptr, d.nR, d.R_min, d.hR}, s);
 }
 
 void launch_single_species(const Dims &d, const Bufs &b, bool both, hipStream_t s, int parts) {
-    const int Np = padded(d.N);
     ZBatch zb{};
     int c = 0;
     auto add = [&](const double2 *X, const double2 *Y, double2 *o, int K, double sc) {
@@ -849,12 +948,10 @@ void launch_single_species(const Dims &d, const Bufs &b, bool both, hipStream_t 
         }
     }
     if (c == 0) return;
-    hipLaunchKernelGGL(d.zoff ? k_zgemm<true> : k_zgemm<false>, dim3(Np / kZT, Np / kZT, c * d.batch), dim3(256), 0, s,
-                       zb, Np, b.flags, c, d.zoff);
+    launch_zgemm(d, zb, c, b.flags, s);
 }
 
 void launch_single_species_next(const Dims &d, const Bufs &b, hipStream_t s) {
-    const int Np = padded(d.N);
     ZBatch zb{};
     zb.X[0] = b.psi1;
     zb.Y[0] = b.G1b;
@@ -866,8 +963,7 @@ void launch_single_species_next(const Dims &d, const Bufs &b, hipStream_t s) {
     zb.out[1] = b.E2b;
     zb.K[1] = d.nR;
     zb.scale[1] = d.hR;
-    hipLaunchKernelGGL(d.zoff ? k_zgemm<true> : k_zgemm<false>, dim3(Np / kZT, Np / kZT, 2 * d.batch), dim3(256), 0, s,
-                       zb, Np, b.flags, 2, d.zoff);
+    launch_zgemm(d, zb, 2, b.flags, s);
 }
 
 // The sum-of-products contraction.  Fewer b per unit where the launch would

@@ -34,15 +34,30 @@ __device__ inline dbl4 mfma_f64(double a, double b, dbl4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-__global__ void k_sinc(const double *__restrict__ pos, int Np, int n, double x_min, double h,
-                       double *__restrict__ S, double *__restrict__ Sp, const int32_t *__restrict__ flags, const long long *__restrict__ zoff) {
+// Tables of one species; both in one launch (grid y).
+struct SincSpecies {
+    const double *pos;
+    int n;
+    double x_min, h;
+    double *S, *Sp;
+};
+
+__global__ void k_sinc(SincSpecies s1, SincSpecies s2, int keep_min, int32_t *__restrict__ flags,
+                       unsigned long long *__restrict__ min_bits, const long long *__restrict__ zoff) {
     const long long zo_ = batch_offset(zoff);
-    pos = zshift(pos, zo_);
-    S = zshift(S, zo_);
-    Sp = zshift(Sp, zo_);
     flags = zshift(flags, zo_);
 
+    // the words k_vel_finish counts into, before it
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+        flags[kFlagOut] = 0;
+        if (!keep_min) *zshift(min_bits, zo_) = 0x7ff0000000000000ULL;   // +inf
+    }
     if (flags[kFlagHalt]) return;
+    const SincSpecies &sp_ = blockIdx.y ? s2 : s1;
+    const double *pos = zshift(sp_.pos, zo_);
+    double *S = zshift(sp_.S, zo_), *Sp = zshift(sp_.Sp, zo_);
+    const int n = sp_.n;
+    const double x_min = sp_.x_min, h = sp_.h;
     __shared__ double red[256];
     const int a = blockIdx.x;
     const int tid = threadIdx.x;
@@ -258,6 +273,133 @@ __global__ void __launch_bounds__(256) k_vel_gemm(const double *__restrict__ Sr,
     }
 }
 
+// The same where 64 x 32 tiles are too few for the device: 16 (a) x 32 (b)
+// per work-group, its eight waves taking the 8-point steps of both grids in
+// turn, operands straight from global memory one step ahead.  The partial
+// sums meet in LDS, a fragment of columns and a species at a time; wave v < 4
+// keeps accumulator register v of all eight of them and forms the three
+// products with C_b.
+constexpr int kVelWaves = 8;
+
+__device__ __forceinline__ void vel_steps(const double *Sg, const double *Dg, const double2 *Pg, int K, int a0, int b0,
+                                          int wave, dbl4 (&acc)[2][4]) {
+    constexpr int EP = 2;                            // consecutive points per lane
+    const int lane = threadIdx.x & 63, row = lane & 15, quarter = lane >> 4;
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[g][i] = dbl4{0, 0, 0, 0};
+    const int count = (K / (4 * EP) - wave + kVelWaves - 1) / kVelWaves;
+    if (count <= 0) return;
+    const gchar *sat = opaque(Sg + (size_t)a0 * K + 4 * EP * wave), *dat = opaque(Dg + (size_t)a0 * K + 4 * EP * wave);
+    const gchar *pat = opaque(Pg + (size_t)b0 * K + 4 * EP * wave);
+    const uint32_t toff = (uint32_t)row * K * 8u + quarter * 8u * EP, poff = 2 * toff, frow = 256u * K;
+    dbl2 s[EP / 2], d[EP / 2], p[2][EP];
+    auto load = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < EP / 2; ++e) {
+            s[e] = *reinterpret_cast<const gdouble2 *>(sat + toff + 16u * e);
+            d[e] = *reinterpret_cast<const gdouble2 *>(dat + toff + 16u * e);
+        }
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int e = 0; e < EP; ++e) p[g][e] = *reinterpret_cast<const gdouble2 *>(pat + (size_t)g * frow + poff + 16u * e);
+        pin_loads();
+    };
+    load();
+    for (int n = 0; n < count; ++n) {
+        dbl2 sc[EP / 2], dc[EP / 2], pc[2][EP];
+#pragma unroll
+        for (int e = 0; e < EP / 2; ++e) {
+            sc[e] = s[e];
+            dc[e] = d[e];
+        }
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int e = 0; e < EP; ++e) pc[g][e] = p[g][e];
+        const size_t st = n + 1 < count ? 32u * EP * kVelWaves : 0;   // the last step loads its own operands again (never used)
+        sat += st;
+        dat += st;
+        pat += 2 * st;
+        load();
+#pragma unroll
+        for (int e = 0; e < EP; ++e)
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                const double sv = sc[e / 2][e & 1], dv = dc[e / 2][e & 1];
+                acc[g][0] = mfma_f64(sv, pc[g][e].x, acc[g][0]);
+                acc[g][1] = mfma_f64(sv, pc[g][e].y, acc[g][1]);
+                acc[g][2] = mfma_f64(dv, pc[g][e].x, acc[g][2]);
+                acc[g][3] = mfma_f64(dv, pc[g][e].y, acc[g][3]);
+            }
+    }
+}
+
+template <bool BATCHED>
+__global__ void __launch_bounds__(64 * kVelWaves) k_vel_split(const double *__restrict__ Sr, const double *__restrict__ Dr,
+                                                              const double2 *__restrict__ psi1, int nr,
+                                                              const double *__restrict__ SR, const double *__restrict__ DR,
+                                                              const double2 *__restrict__ psi2, int nR,
+                                                              const double2 *__restrict__ C, int Np,
+                                                              double2 *__restrict__ part, const int32_t *__restrict__ flags,
+                                                              const long long *__restrict__ zoff) {
+    const long long zo_ = BATCHED ? batch_offset(zoff) : 0;
+    C = zshift(C, zo_);
+    part = zshift(part, zo_);
+    flags = zshift(flags, zo_);
+
+    if (flags[kFlagHalt]) return;
+    __shared__ double red[kVelWaves][16][64];        // [wave][quantity, register v][lane]
+    const int lane = threadIdx.x & 63, row = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int a0 = blockIdx.x * 16, b0 = blockIdx.y * kVB;
+    double sum[2][2][4];                             // [species][column fragment][quantity], waves 0..3
+#pragma unroll
+    for (int sp = 0; sp < 2; ++sp) {
+        dbl4 acc[2][4];
+        vel_steps(zshift(sp ? SR : Sr, zo_), zshift(sp ? DR : Dr, zo_), zshift(sp ? psi2 : psi1, zo_), sp ? nR : nr, a0,
+                  b0, wave, acc);
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            __syncthreads();                         // the previous round's sums are read
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) red[wave][4 * i + v][lane] = acc[g][i][v];
+            __syncthreads();
+            if (wave < 4)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int it = 4 * i + wave;
+                    sum[sp][g][i] = ((red[0][it][lane] + red[1][it][lane]) + (red[2][it][lane] + red[3][it][lane])) +
+                                    ((red[4][it][lane] + red[5][it][lane]) + (red[6][it][lane] + red[7][it][lane]));
+                }
+        }
+    }
+    if (wave >= 4) return;
+    double2 pPsi = make_double2(0.0, 0.0), pr = pPsi, pR = pPsi;
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        const double2 A1 = make_double2(sum[0][g][0], sum[0][g][1]), D1 = make_double2(sum[0][g][2], sum[0][g][3]);
+        const double2 A2 = make_double2(sum[1][g][0], sum[1][g][1]), D2 = make_double2(sum[1][g][2], sum[1][g][3]);
+        const double2 cb = C[b0 + 16 * g + row], cA2 = cmul(cb, A2);
+        pPsi = cadd(pPsi, cmul(cA2, A1));
+        pr = cadd(pr, cmul(cA2, D1));
+        pR = cadd(pR, cmul(cmul(cb, A1), D2));
+    }
+    pPsi = make_double2(row16_sum(pPsi.x), row16_sum(pPsi.y));
+    pr = make_double2(row16_sum(pr.x), row16_sum(pr.y));
+    pR = make_double2(row16_sum(pR.x), row16_sum(pR.y));
+    if (row == 0) {
+        double2 *dst = part + ((size_t)blockIdx.y * Np + a0 + mfma_row_f64(lane, wave)) * 3;
+        dst[0] = pPsi;
+        dst[1] = pr;
+        dst[2] = pR;
+    }
+}
+
 __device__ inline unsigned long long dbits(double x) { return (unsigned long long)__double_as_longlong(x); }
 
 __global__ void k_vel_finish(const double2 *__restrict__ part, int N, int Np, double m_r, double m_R, double dt,
@@ -341,17 +483,6 @@ __global__ void k_vel_finish(const double2 *__restrict__ part, int N, int Np, do
     }
 }
 
-__global__ void k_vel_reset(int32_t *flags, unsigned long long *min_bits, int keep_min, const long long *__restrict__ zoff) {
-    const long long zo_ = batch_offset(zoff);
-    flags = zshift(flags, zo_);
-    min_bits = zshift(min_bits, zo_);
-
-    if (threadIdx.x == 0) {
-        flags[kFlagOut] = 0;
-        if (!keep_min) *min_bits = 0x7ff0000000000000ULL;   // +inf
-    }
-}
-
 }  // namespace
 
 void launch_velocity(const Dims &d, const Bufs &b, VelocityMode mode, hipStream_t s) {
@@ -360,16 +491,24 @@ void launch_velocity(const Dims &d, const Bufs &b, VelocityMode mode, hipStream_
     const double *pr = mode == kVelocityHeun ? b.r_new : b.r;
     const double *pR = mode == kVelocityHeun ? b.R_new : b.R;
     const int B = d.batch;
-    hipLaunchKernelGGL(k_sinc, dim3(Np, 1, B), dim3(256), 0, s, pr, Np, d.nr, d.r_min, d.hr, b.sinc_r, b.dsinc_r,
-                       b.flags, d.zoff);
-    hipLaunchKernelGGL(k_sinc, dim3(Np, 1, B), dim3(256), 0, s, pR, Np, d.nR, d.R_min, d.hR, b.sinc_R, b.dsinc_R,
-                       b.flags, d.zoff);
-    hipLaunchKernelGGL(d.zoff ? k_vel_gemm<true> : k_vel_gemm<false>, dim3(Np / kVA, Np / kVB, B), dim3(256), 0, s, b.sinc_r, b.dsinc_r, b.psi1, d.nr,
-                       b.sinc_R, b.dsinc_R, b.psi2, d.nR, b.C, Np, b.vpart, b.flags, d.zoff);
     unsigned long long *min_bits = reinterpret_cast<unsigned long long *>(b.scal);
     // min |Psi| over the step's evaluations: the corrector keeps the first pass's minimum
-    hipLaunchKernelGGL(k_vel_reset, dim3(1, 1, B), dim3(64), 0, s, b.flags, min_bits, mode == kVelocityHeun ? 1 : 0,
-                       d.zoff);
+    hipLaunchKernelGGL(k_sinc, dim3(Np, 2, B), dim3(256), 0, s, SincSpecies{pr, d.nr, d.r_min, d.hr, b.sinc_r, b.dsinc_r},
+                       SincSpecies{pR, d.nR, d.R_min, d.hR, b.sinc_R, b.dsinc_R}, mode == kVelocityHeun ? 1 : 0, b.flags,
+                       min_bits, d.zoff);
+    // up to 576 padded trajectories (alone or in a batch, which has to give
+    // the same sums) the split kernel: with the tables and k_vel_finish 43
+    // against 99 us at N = 64, 512 x 256, 46 against 102 at N = 250, 73 against
+    // 106 at N = 500, but 218 against 172 at N = 1024, where the tiles fill the
+    // device and read each table row half as often
+    if (Np <= 576)
+        hipLaunchKernelGGL(d.zoff ? k_vel_split<true> : k_vel_split<false>, dim3(Np / 16, Np / kVB, B),
+                           dim3(64 * kVelWaves), 0, s, b.sinc_r, b.dsinc_r, b.psi1, d.nr, b.sinc_R, b.dsinc_R, b.psi2,
+                           d.nR, b.C, Np, b.vpart, b.flags, d.zoff);
+    else
+        hipLaunchKernelGGL(d.zoff ? k_vel_gemm<true> : k_vel_gemm<false>, dim3(Np / kVA, Np / kVB, B), dim3(256), 0, s,
+                           b.sinc_r, b.dsinc_r, b.psi1, d.nr, b.sinc_R, b.dsinc_R, b.psi2, d.nR, b.C, Np, b.vpart,
+                           b.flags, d.zoff);
     const double r_hi = d.r_min + d.hr * d.nr, R_hi = d.R_min + d.hR * d.nR;
     hipLaunchKernelGGL(k_vel_finish, dim3((d.N + 255) / 256, 1, B), dim3(256), 0, s, b.vpart, d.N, Np, d.m_r, d.m_R,
                        d.dt, b.r, b.R, b.r_new, b.R_new, b.v_r, b.v_R, b.psi_at, d.r_min, r_hi, d.R_min, R_hi, d.mp,
