@@ -17,6 +17,7 @@ struct Dims {
     int N, nr, nR, n_bo, prec;
     int lr_rank;                          // terms of the sum of products of W_c the contraction uses
     int products;                         // the contraction is that sum alone (exact to the table's rounding)
+    int bilinear;                         // W_c = lam r R (the cavity): Eqs. 9b-9d from the matrices of r and R
     int fp32_residual;                    // mixed form: the residual left to FP32 is not negligible
     int sinv;                             // RK4 stages through explicit inverses of S + eps I
     int propagator;                       // 0 split operator, 1 Crank-Nicolson
@@ -90,7 +91,8 @@ struct Bufs {
     double2 *G1a, *G1b;                   // [N][nr] W_c(r_i, R^a) psi_1^a_i at x_k, x_k+1
     double2 *G2a, *G2b;                   // [N][nR] W_c(r^a, R_j) psi_2^a_j at x_k, x_k+1
     double2 *S1, *S2;                     // [N][N] single-species overlaps
-    double2 *E1a, *E1b, *E2a, *E2b;       // [N][N] W_c-conditioned single-species integrals
+    double2 *E1a, *E1b, *E2a, *E2b;       // [N][N] W_c-conditioned single-species integrals; with a bilinear
+                                          // W_c, E1a and E2a hold <b|r|a> and <b|R|a>, from which they follow
     double2 *Wc;                          // [N][N] two-body contraction (W_c part of Eq. 9b)
     double2 *Smat[2], *Kmat[2];           // S_k, K_k (current / next by step parity)
     double2 *Kminus, *Kmid;               // K(psi_k+1, x_k) and the midpoint K
@@ -181,7 +183,8 @@ void launch_cond_kets_next(const Dims &d, const Bufs &b, hipStream_t s);
 // Batched h * conj(X) Y^T complex products: the overlaps S1, S2 (parts &
 // kSingleOverlaps: all that S needs) and the coupling integrals E1a, E2a
 // and, with both_conditionings, E1b, E2b (parts & kSingleCouplings: needed by
-// K only).
+// K only).  With a bilinear W_c <b|r|a> and <b|R|a> come with the overlaps and
+// there are no further coupling integrals.
 enum SingleParts { kSingleOverlaps = 1, kSingleCouplings = 2, kSingleAll = 3 };
 void launch_single_species(const Dims &d, const Bufs &b, bool both_conditionings, hipStream_t s,
                            int parts = kSingleAll);

@@ -76,6 +76,8 @@ struct ZBatch {
     double2 *out[6];
     int K[6];
     double scale[6];
+    double w0[6], w1[6];     // weight w0 + w1 k of the reduction's point k (weighted == 0: none)
+    int weighted[6];
 };
 
 // Work-group of 4 waves per 64 x 64 output tile, wave w on the 32 x 32
@@ -101,6 +103,29 @@ __device__ inline T zpick(const T (&a)[6], int z) {
     return r;
 }
 
+__device__ inline void triangle_tile(int t, int *tb, int *ta) {
+    int a = (int)((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
+    while ((a + 1) * (a + 2) / 2 <= t) ++a;
+    while (a * (a + 1) / 2 > t) --a;
+    *ta = a;
+    *tb = t - a * (a + 1) / 2;
+}
+
+// Output tile (bt, at) of a launch over nt x nt tiles: by rows, or of a
+// Hermitian output its upper tiles one after the other (a run of work-groups
+// goes round the XCDs: by rows, the XCDs of the last columns had a fifth more
+// than their share).  False: none left.
+__device__ inline bool zgemm_tile(int t, int nt, bool herm, int *bt, int *at) {
+    if (!herm) {
+        *bt = t / nt;
+        *at = t - *bt * nt;
+        return true;
+    }
+    if (t >= nt * (nt + 1) / 2) return false;
+    triangle_tile(t, bt, at);
+    return true;
+}
+
 template <bool BATCHED>
 __global__ void __launch_bounds__(256, 2) k_zgemm(ZBatch zb, int Np, const int32_t *__restrict__ flags, int zcnt,
                                                   const long long *__restrict__ zoff) {
@@ -109,11 +134,11 @@ __global__ void __launch_bounds__(256, 2) k_zgemm(ZBatch zb, int Np, const int32
     const long long zo_ = BATCHED ? batch_offset(zoff, sim) : 0;
     flags = zshift(flags, zo_);
     if (flags[kFlagHalt]) return;
-    const int bt = blockIdx.y, at = blockIdx.x;
     const double2 *__restrict__ X = zshift(zpick(zb.X, z), zo_);
     const double2 *__restrict__ Y = zshift(zpick(zb.Y, z), zo_);
     const bool herm = X == Y;   // the output is Hermitian: upper tiles only
-    if (herm && bt > at) return;
+    int bt, at;
+    if (!zgemm_tile(blockIdx.x, Np / kZT, herm, &bt, &at)) return;
     __shared__ double2 sX[2][kZT][kZLD];
     __shared__ double2 sY[2][kZT][kZLD];
     const int K = zpick(zb.K, z);
@@ -134,8 +159,19 @@ __global__ void __launch_bounds__(256, 2) k_zgemm(ZBatch zb, int Np, const int32
     const double2 *xs = X + (size_t)(b0 + srow) * K + sk;   // rows srow + 16 m
     const double2 *ys = Y + (size_t)(a0 + srow) * K + sk;
     const size_t rstep = (size_t)16 * K;
+    const bool weighted = zpick(zb.weighted, z) != 0;
+    const double w0 = zpick(zb.w0, z), w1 = zpick(zb.w1, z);
     double2 rx0 = xs[0], rx1 = xs[rstep], rx2 = xs[2 * rstep], rx3 = xs[3 * rstep];
     double2 ry0 = ys[0], ry1 = ys[rstep], ry2 = ys[2 * rstep], ry3 = ys[3 * rstep];
+    auto weigh = [&](int k0) __attribute__((always_inline)) {
+        if (!weighted) return;
+        const double w = w0 + w1 * (k0 + sk);
+        ry0 = cscale(ry0, w);
+        ry1 = cscale(ry1, w);
+        ry2 = cscale(ry2, w);
+        ry3 = cscale(ry3, w);
+    };
+    weigh(0);
     sX[0][srow][sk] = rx0;
     sX[0][srow + 16][sk] = rx1;
     sX[0][srow + 32][sk] = rx2;
@@ -182,6 +218,7 @@ __global__ void __launch_bounds__(256, 2) k_zgemm(ZBatch zb, int Np, const int32
         }
         if (more) {
             const int nb = buf ^ 1;
+            weigh((ch + 1) * kZKC);
             sX[nb][srow][sk] = rx0;
             sX[nb][srow + 16][sk] = rx1;
             sX[nb][srow + 32][sk] = rx2;
@@ -222,12 +259,14 @@ __global__ void __launch_bounds__(256, 2) k_zgemm_split(ZBatch zb, int Np, const
     const long long zo_ = BATCHED ? batch_offset(zoff, sim) : 0;
     flags = zshift(flags, zo_);
     if (flags[kFlagHalt]) return;
-    const int bt = blockIdx.y, at = blockIdx.x;
     const double2 *X = zshift(zpick(zb.X, z), zo_);
     const double2 *Y = zshift(zpick(zb.Y, z), zo_);
     const bool herm = X == Y;   // the output is Hermitian: upper tiles only
-    if (herm && bt > at) return;
     constexpr int W = 4, T = 16 * F, EP = 4, ITEMS = 4 * F * F;
+    int bt, at;
+    if (!zgemm_tile(blockIdx.x, Np / T, herm, &bt, &at)) return;
+    bt = __builtin_amdgcn_readfirstlane(bt);
+    at = __builtin_amdgcn_readfirstlane(at);
     __shared__ double2 red[W][ITEMS][64];
     const int K = zpick(zb.K, z);
     const int t = threadIdx.x, lane = t & 63, row = lane & 15, quarter = lane >> 4;
@@ -259,6 +298,9 @@ __global__ void __launch_bounds__(256, 2) k_zgemm_split(ZBatch zb, int Np, const
             pin_loads();
         };
         load();
+        const bool weighted = zpick(zb.weighted, z) != 0;
+        const double w0 = zpick(zb.w0, z), w1 = zpick(zb.w1, z);
+        int k = 4 * EP * wave + EP * quarter;
         for (int s = 0; s < count; ++s) {
             dbl2 xc[F][EP], yc[F][EP];
 #pragma unroll
@@ -268,6 +310,15 @@ __global__ void __launch_bounds__(256, 2) k_zgemm_split(ZBatch zb, int Np, const
                     xc[f][e] = x[f][e];
                     yc[f][e] = y[f][e];
                 }
+            if (weighted) {
+#pragma unroll
+                for (int e = 0; e < EP; ++e) {
+                    const double w = w0 + w1 * (k + e);
+#pragma unroll
+                    for (int f = 0; f < F; ++f) yc[f][e] *= w;
+                }
+                k += 4 * EP * W;
+            }
             const size_t st = s + 1 < count ? W * kStep : 0;  // the last step loads its own operands again (never used)
             xat += st;
             yat += st;
@@ -317,7 +368,8 @@ __global__ void __launch_bounds__(256, 2) k_zgemm_split(ZBatch zb, int Np, const
 static void launch_zgemm(const Dims &d, const ZBatch &zb, int c, const int32_t *flags, hipStream_t s) {
     const int Np = padded(d.N);
     auto go = [&](auto kernel, int T) {
-        hipLaunchKernelGGL(kernel, dim3(Np / T, Np / T, c * d.batch), dim3(256), 0, s, zb, Np, flags, c, d.zoff);
+        hipLaunchKernelGGL(kernel, dim3((Np / T) * (Np / T), 1, c * d.batch), dim3(256), 0, s, zb, Np, flags, c,
+                           d.zoff);
     };
     if (Np > 768) go(d.zoff ? k_zgemm<true> : k_zgemm<false>, kZT);
     else if ((long long)c * d.batch * (Np / 32) * (Np / 32) <= 256)
@@ -338,14 +390,6 @@ struct WcTraits<float> {
     typedef flt4 acc4;
     typedef float2 cplx;    // FP32 copy of psi1 (written by the propagation)
 };
-
-__device__ inline void triangle_tile(int t, int *tb, int *ta) {
-    int a = (int)((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
-    while ((a + 1) * (a + 2) / 2 <= t) ++a;
-    while (a * (a + 1) / 2 > t) --a;
-    *ta = a;
-    *tb = t - a * (a + 1) / 2;
-}
 
 // Block = 4 waves on a 16 (b) x 16 (a) tile of the upper triangle (tile
 // index tb <= ta); wave w owns b = b_tile + 4w .. 4w + 3 against all 16 a.
@@ -908,6 +952,7 @@ std::vector<int32_t> wc_tile_order(int Np) {
 }
 
 static void launch_kets(const Dims &d, const Bufs &b, const CondSpecies &s1, const CondSpecies &s2, hipStream_t s) {
+    if (d.bilinear) return;
     const int Np = padded(d.N);
     const unsigned blocks1 = (unsigned)(((size_t)Np * d.nr + 255) / 256), blocks2 = (unsigned)(((size_t)Np * d.nR + 255) / 256);
     hipLaunchKernelGGL(k_cond_kets, dim3(blocks1 + blocks2, 1, d.batch), dim3(256), 0, s, s1, s2, blocks1, d.mp, Np,
@@ -937,21 +982,32 @@ void launch_single_species(const Dims &d, const Bufs &b, bool both, hipStream_t 
     };
     if (parts & kSingleOverlaps) {
         add(b.psi1, b.psi1, b.S1, d.nr, d.hr);
-        add(b.psi2, b.psi2, b.S2, d.nR, d.hR);
-    }
-    if (parts & kSingleCouplings) {
-        add(b.psi1, b.G1a, b.E1a, d.nr, d.hr);
-        add(b.psi2, b.G2a, b.E2a, d.nR, d.hR);
-        if (both) {
-            add(b.psi1, b.G1b, b.E1b, d.nr, d.hr);
-            add(b.psi2, b.G2b, b.E2b, d.nR, d.hR);
+        if (d.bilinear) {
+            add(b.psi1, b.psi1, b.E1a, d.nr, d.hr);
+            zb.weighted[1] = 1;
+            zb.w0[1] = d.r_min;
+            zb.w1[1] = d.hr;
         }
+        add(b.psi2, b.psi2, b.S2, d.nR, d.hR);
+        if (d.bilinear) {
+            add(b.psi2, b.psi2, b.E2a, d.nR, d.hR);
+            zb.weighted[3] = 1;
+            zb.w0[3] = d.R_min;
+            zb.w1[3] = d.hR;
+        }
+    }
+    if ((parts & kSingleCouplings) && !d.bilinear) {
+        add(b.psi1, b.G1a, b.E1a, d.nr, d.hr);
+        if (both) add(b.psi1, b.G1b, b.E1b, d.nr, d.hr);
+        add(b.psi2, b.G2a, b.E2a, d.nR, d.hR);
+        if (both) add(b.psi2, b.G2b, b.E2b, d.nR, d.hR);
     }
     if (c == 0) return;
     launch_zgemm(d, zb, c, b.flags, s);
 }
 
 void launch_single_species_next(const Dims &d, const Bufs &b, hipStream_t s) {
+    if (d.bilinear) return;
     ZBatch zb{};
     zb.X[0] = b.psi1;
     zb.Y[0] = b.G1b;
@@ -986,6 +1042,7 @@ static void launch_wc_sep(const Dims &d, const Bufs &b, int accumulate, hipStrea
 }
 
 void launch_wc(const Dims &d, const Bufs &b, hipStream_t s) {
+    if (d.bilinear) return;                          // the assembly multiplies <b|r|a> by <b|R|a>
     const int Np = padded(d.N);
     const int T16 = Np / 16;
     const int blocks = T16 * (T16 + 1) / 2;

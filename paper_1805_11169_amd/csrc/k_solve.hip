@@ -5,7 +5,8 @@
 // Eq. 9b cancel against Eqs. 9c-9d except at the ket's own trajectory:
 //     K[b][a] = Wc[b][a] - E1[b][a] S2[b][a] - S1[b][a] E2[b][a]
 //               - (V_1(r^a) + V_2(R^a)) S[b][a],     S = S1 o S2,
-// where Wc, E1, E2 are the Eq. 9b-9d integrals with W_c alone.  Per step the
+// where Wc, E1, E2 are the Eq. 9b-9d integrals with W_c alone (with a bilinear
+// W_c, from the matrices of r and R).  Per step the
 // kernel forms S_k+1, K^- = K(psi_k+1, x_k) (end of the step just taken),
 // K_k+1 = K(psi_k+1, x_k+1) (start of the next), the midpoint averages, and
 // the regularised matrices handed to the factorisation.
@@ -42,7 +43,7 @@ __device__ inline dbl4 mfma(double a, double b, dbl4 c) {
 __global__ void k_assemble(const double2 *__restrict__ S1, const double2 *__restrict__ S2,
                            const double2 *__restrict__ E1a, const double2 *__restrict__ E1b,
                            const double2 *__restrict__ E2a, const double2 *__restrict__ E2b,
-                           const double2 *__restrict__ Wc, const double2 *__restrict__ Scur,
+                           double2 *__restrict__ Wc, int bilinear, const double2 *__restrict__ Scur,
                            const double2 *__restrict__ Kcur, const double *__restrict__ r,
                            const double *__restrict__ R, const double *__restrict__ r_new,
                            const double *__restrict__ R_new, ModelParams mp, int N, int Np, double eps,
@@ -88,14 +89,29 @@ __global__ void k_assemble(const double2 *__restrict__ S1, const double2 *__rest
         }
     }
     if (!(part & kAssembleK)) return;
-    const double2 w = (b <= a) ? Wc[idx] : cconj(Wc[(size_t)a * Np + b]);
+    double2 w, e1, e2;
+    if (bilinear) {
+        // W_c = lam r R: e1, e2 = <b|r|a>, <b|R|a>; the matrices of Eqs. 9b-9d
+        // are lam times their product and lam R^a e1, lam r^a e2
+        e1 = E1a[idx];
+        e2 = E2a[idx];
+        w = cscale(cmul(e1, e2), mp.p[3]);
+        if (part != kAssembleKnext) Wc[idx] = w;
+    } else {
+        w = (b <= a) ? Wc[idx] : cconj(Wc[(size_t)a * Np + b]);
+    }
+    auto coupling = [&](const double2 *e1_at, const double2 *e2_at, double ra, double Ra, double c) {
+        const double2 x1 = bilinear ? cscale(e1, mp.p[3] * Ra) : e1_at[idx];
+        const double2 x2 = bilinear ? cscale(e2, mp.p[3] * ra) : e2_at[idx];
+        return csub(csub(csub(w, cmul(x1, s2)), cmul(s1, x2)), cscale(S, c));
+    };
     double ca = 0.0, cn = 0.0;
     if (a < N) {
         ca = model_v1(mp, r[a]) + model_v2(mp, R[a]);
         cn = model_v1(mp, r_new[a]) + model_v2(mp, R_new[a]);
     }
     if (part != kAssembleKnext) {
-        const double2 km = csub(csub(csub(w, cmul(E1a[idx], s2)), cmul(s1, E2a[idx])), cscale(S, ca));
+        const double2 km = coupling(E1a, E2a, r[a], R[a], ca);
         if (part == kAssembleInitial) {
             // start of the run: K_0 = K(psi_0, x_0) -> the slot of parity 0
             Knext[idx] = km;
@@ -105,8 +121,7 @@ __global__ void k_assemble(const double2 *__restrict__ S1, const double2 *__rest
         const double2 kc = Kcur[idx];
         Kmid[idx] = make_double2(0.5 * (kc.x + km.x), 0.5 * (kc.y + km.y));
     }
-    if (part != kAssembleKminus)
-        Knext[idx] = csub(csub(csub(w, cmul(E1b[idx], s2)), cmul(s1, E2b[idx])), cscale(S, cn));
+    if (part != kAssembleKminus) Knext[idx] = coupling(E1b, E2b, r_new[a], R_new[a], cn);
 }
 
 // ------------------------------------------------------------------ Cholesky
@@ -1079,7 +1094,7 @@ void launch_assemble(const Dims &d, const Bufs &b, int parity, AssemblePart part
     const bool initial = part == kAssembleInitial;
     const int cur = parity, nxt = initial ? parity : 1 - parity;
     hipLaunchKernelGGL(k_assemble, dim3((unsigned)((tot + 255) / 256), 1, d.batch), dim3(256), 0, s, b.S1, b.S2,
-                       b.E1a, b.E1b, b.E2a, b.E2b, b.Wc, b.Smat[cur], b.Kmat[cur], b.r, b.R, b.r_new, b.R_new, d.mp,
+                       b.E1a, b.E1b, b.E2a, b.E2b, b.Wc, d.bilinear, b.Smat[cur], b.Kmat[cur], b.r, b.R, b.r_new, b.R_new, d.mp,
                        d.N, Np, d.eps, (int)part, b.Smat[nxt], b.Kminus, b.Kmat[nxt], b.Lmid, b.L[nxt], b.Kmid, b.flags,
                        d.zoff, d.mpd);
 }
