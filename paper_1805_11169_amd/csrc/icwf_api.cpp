@@ -39,8 +39,6 @@ struct Layout {
     }
 };
 
-size_t obs_len(int nr, int nR, int n_bo) { return 1 + (size_t)nr + nR + n_bo + (size_t)n_bo * n_bo; }
-
 Bufs carve(const icwf_config &c, char *base, size_t *total) {
     Layout L;
     L.base = base;
@@ -111,7 +109,7 @@ Bufs carve(const icwf_config &c, char *base, size_t *total) {
     b.obs_psi = L.take<double2>(nr * nR);
     b.obs_chi = L.take<double2>(std::max<size_t>(1, nbo * nR));
     b.obs_part = L.take<double>(icwf::kRhoSlices * nR);
-    b.obs_out = L.take<double>(obs_len(c.n_r, c.n_R, c.n_bo));
+    b.obs_out = L.take<double>(icwf::obs_len(c.n_r, c.n_R, c.n_bo) + icwf::obs_tail_len(c.n_traj));
     b.mparams = L.take<icwf::ModelParams>(1);
     b.batch_tab = L.take<long long>(icwf::kMaxBatch);
     *total = (L.off + 255) & ~size_t(255);
@@ -382,10 +380,7 @@ void enqueue_step(icwf_sim *s, const Dims &d, int parity, hipStream_t st, hipStr
     }
 }
 
-icwf_status device_status(icwf_sim *s) {
-    int32_t flags[icwf::kNumFlags];
-    HIP_OK(hipMemcpyAsync(flags, s->b.flags, sizeof(flags), hipMemcpyDeviceToHost, s->stream), s);
-    HIP_OK(hipStreamSynchronize(s->stream), s);
+icwf_status status_of(icwf_sim *s, const int32_t *flags) {
     if (flags[icwf::kFlagNode]) {
         s->status = ICWF_ENODE;
         return fail(s, ICWF_ENODE, "a trajectory sits at a node of the ansatz wavefunction (|Psi| < 1e-300)");
@@ -403,6 +398,13 @@ icwf_status device_status(icwf_sim *s) {
         return fail(s, ICWF_ENONFINITE, "non-finite value in the coefficients or positions");
     }
     return ICWF_OK;
+}
+
+icwf_status device_status(icwf_sim *s) {
+    int32_t flags[icwf::kNumFlags];
+    HIP_OK(hipMemcpyAsync(flags, s->b.flags, sizeof(flags), hipMemcpyDeviceToHost, s->stream), s);
+    HIP_OK(hipStreamSynchronize(s->stream), s);
+    return status_of(s, flags);
 }
 
 icwf_status capture_graphs(icwf_sim *s) {
@@ -840,17 +842,18 @@ icwf_status icwf_sync(icwf_sim *s) {
 
 icwf_status icwf_observables(icwf_sim *s, icwf_obs *o) {
     if (!s || !o) return fail(s, ICWF_EINVAL, "NULL argument");
-    icwf_status st = icwf_sync(s);
     const Dims &d = s->d;
     icwf::launch_observables(d, s->b, s->stream);
     HIP_OK(hipGetLastError(), s);
-    std::vector<double> buf(obs_len(d.nr, d.nR, d.n_bo));
+    // everything in one copy: the observables, r, R, C, the scalars, the flags
+    const size_t len = icwf::obs_len(d.nr, d.nR, d.n_bo);
+    std::vector<double> buf(len + icwf::obs_tail_len(d.N));
     HIP_OK(hipMemcpyAsync(buf.data(), s->b.obs_out, sizeof(double) * buf.size(), hipMemcpyDeviceToHost, s->stream), s);
-    int32_t flags[icwf::kNumFlags];
-    double scal[8];
-    HIP_OK(hipMemcpyAsync(flags, s->b.flags, sizeof(flags), hipMemcpyDeviceToHost, s->stream), s);
-    HIP_OK(hipMemcpyAsync(scal, s->b.scal, sizeof(scal), hipMemcpyDeviceToHost, s->stream), s);
     HIP_OK(hipStreamSynchronize(s->stream), s);
+    const double *tail = buf.data() + len, *scal = tail + 4 * (size_t)d.N;
+    int32_t flags[icwf::kNumFlags];
+    std::memcpy(flags, scal + icwf::kObsScalars, sizeof(flags));
+    const icwf_status st = s->status != ICWF_OK ? static_cast<icwf_status>(s->status) : status_of(s, flags);
     o->t = s->t;
     o->step = s->step;
     o->norm = buf[0];
@@ -859,16 +862,11 @@ icwf_status icwf_observables(icwf_sim *s, icwf_obs *o) {
     const size_t po = 1 + d.nr + d.nR;
     if (o->pop && d.n_bo) std::copy(buf.begin() + po, buf.begin() + po + d.n_bo, o->pop);
     if (o->D && d.n_bo) std::copy(buf.begin() + po + d.n_bo, buf.begin() + po + d.n_bo + d.n_bo * d.n_bo, o->D);
-    if (o->r) HIP_OK(hipMemcpyAsync(o->r, s->b.r, sizeof(double) * d.N, hipMemcpyDeviceToHost, s->stream), s);
-    if (o->R) HIP_OK(hipMemcpyAsync(o->R, s->b.R, sizeof(double) * d.N, hipMemcpyDeviceToHost, s->stream), s);
-    if (o->C) HIP_OK(hipMemcpyAsync(o->C, s->b.C, sizeof(double2) * d.N, hipMemcpyDeviceToHost, s->stream), s);
-    HIP_OK(hipStreamSynchronize(s->stream), s);
+    if (o->r) std::copy(tail, tail + d.N, o->r);
+    if (o->R) std::copy(tail + d.N, tail + 2 * (size_t)d.N, o->R);
+    if (o->C) std::copy(tail + 2 * (size_t)d.N, tail + 4 * (size_t)d.N, o->C);
     o->n_out_of_box = flags[icwf::kFlagOut];
-    uint64_t bits;
-    std::memcpy(&bits, &scal[0], sizeof(bits));
-    double mn;
-    std::memcpy(&mn, &bits, sizeof(mn));
-    o->min_abs_psi = (s->step == 0) ? INFINITY : mn;
+    o->min_abs_psi = (s->step == 0) ? INFINITY : scal[0];
     return st;
 }
 
@@ -1024,7 +1022,7 @@ icwf::ExactBufs carve_exact(const icwf_config &c, char *base, size_t *total, dou
     *bo = L.take<double>(std::max<size_t>(1, nR * nbo * nr));
     *chi = L.take<double2>(std::max<size_t>(1, nbo * nR));
     *part = L.take<double>(icwf::kRhoSlices * nR);
-    *out = L.take<double>(obs_len(c.n_r, c.n_R, c.n_bo));
+    *out = L.take<double>(icwf::obs_len(c.n_r, c.n_R, c.n_bo));
     *total = (L.off + 255) & ~size_t(255);
     return e;
 }
@@ -1127,7 +1125,7 @@ icwf_status icwf_exact_observables(icwf_exact *x, icwf_obs *o) {
     if (!x || !o) return fail(nullptr, ICWF_EINVAL, "NULL argument");
     const int nr = x->cfg.n_r, nR = x->cfg.n_R, nbo = x->cfg.n_bo;
     icwf::launch_grid_observables(x->e.psi, nr, nR, x->hr, x->hR, nbo, x->bo, x->chi, x->part, x->out, x->stream);
-    std::vector<double> buf(obs_len(nr, nR, nbo));
+    std::vector<double> buf(icwf::obs_len(nr, nR, nbo));
     if (hipMemcpyAsync(buf.data(), x->out, sizeof(double) * buf.size(), hipMemcpyDeviceToHost, x->stream) != hipSuccess ||
         hipStreamSynchronize(x->stream) != hipSuccess)
         return fail(nullptr, ICWF_EDEVICE, "observables copy failed");

@@ -234,7 +234,12 @@ void launch_solve_reset(const Dims &d, const Bufs &b, hipStream_t s);
 // Copy x_k+1 -> x_k (end of a step).
 void launch_commit_positions(const Dims &d, const Bufs &b, hipStream_t s);
 
-// Observables into b.obs_out (layout in icwf_api.cpp).
+// Observables [norm, rho_r[nr], rho_R[nR], pop[n_bo], D[n_bo][n_bo]] into
+// b.obs_out, and behind them [r[N], R[N], C[N] (complex), kObsScalars scalars,
+// kNumFlags int32 flags].
+constexpr int kObsScalars = 8;
+inline size_t obs_len(int nr, int nR, int n_bo) { return 1 + (size_t)nr + nR + n_bo + (size_t)n_bo * n_bo; }
+inline size_t obs_tail_len(int N) { return 4 * (size_t)N + kObsScalars + kNumFlags / 2; }
 void launch_observables(const Dims &d, const Bufs &b, hipStream_t s);
 
 // Observables of a wavefunction given on the grid, Psi [nr][nR] complex128:

@@ -231,6 +231,25 @@ __global__ void k_obs_pop(const double2 *__restrict__ chi, int nR, int n_bo, dou
     }
 }
 
+// What an observables call returns beside the observables, behind them in one
+// array, so that it all comes back in one copy: r[N], R[N], C[N], the scalars
+// and the flags.
+__global__ void k_obs_tail(const double *__restrict__ r, const double *__restrict__ R, const double2 *__restrict__ C,
+                           const double *__restrict__ scal, const int32_t *__restrict__ flags, int N,
+                           double *__restrict__ tail) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < N) {
+        tail[i] = r[i];
+        tail[N + i] = R[i];
+        const double2 c = C[i];
+        tail[2 * N + 2 * i] = c.x;
+        tail[2 * N + 2 * i + 1] = c.y;
+    }
+    if (blockIdx.x == 0 && threadIdx.x < kObsScalars) tail[4 * N + threadIdx.x] = scal[threadIdx.x];
+    if (blockIdx.x == 0 && threadIdx.x < kNumFlags)
+        reinterpret_cast<int32_t *>(tail + 4 * N + kObsScalars)[threadIdx.x] = flags[threadIdx.x];
+}
+
 }  // namespace
 
 void launch_grid_observables(const double2 *Psi, int nr, int nR, double hr, double hR, int n_bo, const double *bo,
@@ -252,6 +271,8 @@ void launch_observables(const Dims &d, const Bufs &b, hipStream_t s) {
     const dim3 tiles((d.nR + kOT - 1) / kOT, (d.nr + kOT - 1) / kOT);
     hipLaunchKernelGGL(k_obs_psi, tiles, dim3(256), 0, s, b.psi1, b.psi2, b.C, d.nr, d.nR, Np, b.obs_psi);
     launch_grid_observables(b.obs_psi, d.nr, d.nR, d.hr, d.hR, d.n_bo, b.bo, b.obs_chi, b.obs_part, b.obs_out, s);
+    double *tail = b.obs_out + obs_len(d.nr, d.nR, d.n_bo);
+    hipLaunchKernelGGL(k_obs_tail, dim3((d.N + 255) / 256), dim3(256), 0, s, b.r, b.R, b.C, b.scal, b.flags, d.N, tail);
 }
 
 }  // namespace icwf

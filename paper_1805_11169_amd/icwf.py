@@ -176,6 +176,20 @@ def _ptr(a):
     return None if a is None else a.ctypes.data_as(_DP)
 
 
+def _result(shape, dtype):
+    """An array for a result the library copies out of device memory: from 64 KiB
+    in page-locked memory (PyTorch's cached allocator; the copy then runs at the
+    bus's rate and touches no fresh pages: 33.5 MB in 0.60 instead of 3.15 ms),
+    ordinary memory where none is to be had."""
+    import torch
+    if np.dtype(dtype).itemsize * int(np.prod(shape)) >= 1 << 16:
+        try:
+            return torch.empty(tuple(shape), dtype=getattr(torch, np.dtype(dtype).name), pin_memory=True).numpy()
+        except RuntimeError:
+            pass
+    return np.zeros(shape, dtype)
+
+
 def _f64(a, n=None):
     """Contiguous float64 view; complex arrays become interleaved (re, im)."""
     if a is None:
@@ -249,7 +263,7 @@ def bo_states(cfg, R_values, n_states, tol=0.0, max_iter=0, device=0, check=True
     ws = torch.empty(nbytes + 256, dtype=torch.uint8, device=dev)
     aligned = (ws.data_ptr() + 255) & ~255
     stream = torch.cuda.current_stream(dev)
-    states = np.zeros((nv, int(n_states), cfg.n_r))
+    states = _result((nv, int(n_states), cfg.n_r), np.float64)
     energies = np.zeros((nv, int(n_states)))
     info = BoInfo(float(tol), int(max_iter), 0, 0.0, 0)
     st = L.icwf_bo_states(byref(cfg), _ptr(Rv), nv, int(n_states), _ptr(states), _ptr(energies), c_void_p(aligned),
@@ -333,7 +347,7 @@ class Simulation:
     def state(self):
         N, nr, nR = self.N, self.n_r, self.n_R
         r, R = np.zeros(N), np.zeros(N)
-        p1, p2 = np.zeros((N, nr), np.complex128), np.zeros((N, nR), np.complex128)
+        p1, p2 = _result((N, nr), np.complex128), _result((N, nR), np.complex128)
         C = np.zeros(N, np.complex128)
         self._check(lib().icwf_get_state(self.h, _ptr(r), _ptr(R), _ptr(p1.view(np.float64)),
                                          _ptr(p2.view(np.float64)), _ptr(C.view(np.float64))))
@@ -341,7 +355,7 @@ class Simulation:
 
     def matrices(self):
         N = self.N
-        S, K, W = (np.zeros((N, N), np.complex128) for _ in range(3))
+        S, K, W = (_result((N, N), np.complex128) for _ in range(3))
         self._check(lib().icwf_get_matrices(self.h, _ptr(S.view(np.float64)), _ptr(K.view(np.float64)),
                                             _ptr(W.view(np.float64))))
         return S, K, W
@@ -429,7 +443,7 @@ class ExactPropagator:
         return res
 
     def psi(self):
-        p = np.zeros((self.n_r, self.n_R), np.complex128)
+        p = _result((self.n_r, self.n_R), np.complex128)
         self._check(lib().icwf_exact_get_psi(self.h, _ptr(p.view(np.float64))))
         return p
 
