@@ -7,21 +7,31 @@
 // launch:
 //   * h_e is applied through the spectral kinetic operator, two real vectors
 //     per complex transform (T is real and even in k, so T(u + i v) =
-//     T u + i T v): a radix-2 transform in LDS, decimation in time from
-//     bit-reversed input to natural order forward, the multiplier k^2/2m in
-//     natural order, decimation in frequency back to bit-reversed order, then
-//     + W(r_i, R_j) u_i;
+//     T u + i T v), in LDS: decimation in frequency from natural to
+//     bit-reversed order forward, the multiplier k^2/2m in that order, decimation
+//     in time back, then + W(r_i, R_j) u_i.  Up to 1024 points every wave has a
+//     transform of its own, eight points per lane and pass (three radix-2 stages
+//     in registers between two LDS exchanges) and no barrier; above, the
+//     work-group shares one, a stage at a time;
 //   * the preconditioner is (T_spec + c)^-1, the same transforms with the
 //     multiplier 1/(k^2/2m + c), c = max(1, max W - min W) on the grid;
-//   * each iteration orthonormalises [X, P(residuals), previous directions]
-//     by classical Gram-Schmidt run twice (columns that lose all but 1e-10 of
-//     their norm are dropped), applies h_e to the whole basis afresh, forms
-//     the projected matrix and diagonalises it by cyclic Jacobi (parallel
-//     round-robin ordering, rotations of Golub and Van Loan's symmetric 2 x 2
-//     Schur form), then takes the m lowest Ritz pairs as the new block, the
-//     non-X part of their coefficients as the new directions, and the
-//     residuals h_e x - theta x;
+//   * each iteration orthonormalises [X, P(residuals), previous directions] as
+//     one block, twice: the Gram matrix of the unit columns by matrix products,
+//     its Cholesky factor R (columns that keep less than 1e-7 of their norm are
+//     dropped), C R^-1 by substitution; the second time mends what the first
+//     leaves for columns that are nearly dependent.  Then h_e is applied to the
+//     whole basis afresh, the projected matrix (matrix products again) is
+//     diagonalised by cyclic Jacobi (parallel round-robin ordering), and the m
+//     lowest Ritz pairs are the new block, the non-X part of their coefficients
+//     the new directions, h_e x - theta x the residuals;
 //   * it stops when every wanted residual norm is at most tol.
+// What bounds it is latency: some 40 iterations of dependent small phases per
+// R_j, one work-group per compute unit.  512 points, 256 values of R, 3 states,
+// whole calls: 20.7 ms with a dot product and two barriers per pair of columns,
+// rotations by divisions and roots with a barrier per phase, and transforms by
+// the work-group; 4.5 ms now (orthonormalisation 7.2 -> 0.9 ms, Jacobi 3.7 ->
+// 1.1, projected matrix 2.7 -> 0.25, h_e 1.6 -> 0.7).  1024 points, 128 values,
+// 2 states: 20.6 -> 6.6 ms; 128 points, 64 values, 3 states: 13.1 -> 2.8 ms.
 // Vectors live in a per-R_j slice of the caller's workspace (L2-resident
 // during the work-group's life); the transform buffer, the projected matrix
 // and its rotations live in LDS.
@@ -58,14 +68,28 @@ struct BoArgs {
     int32_t *flags;          // kFlagNonfinite on a non-finite potential
 };
 
-// Doubles of one R_j's slice: V, Z, HZ (kBoMaxZ columns each), X, P, Wr
-// (kBoMaxBlock columns each).
-inline size_t bo_stride(int n) { return (size_t)n * (1 + 2 * kBoMaxZ + 3 * kBoMaxBlock); }
+// Doubles of one R_j's slice: V, Z, HZ (kBoMaxZ columns each).
+inline size_t bo_stride(int n) { return (size_t)n * (1 + 2 * kBoMaxZ); }
+
+// 1 / sqrt(x) of a normal x > 0: the hardware's estimate y, with e = 1 - x y^2
+// small, times (1 - e)^-1/2 to second order.
+__device__ __forceinline__ double inverse_root(double x) {
+    const double y = __builtin_amdgcn_rsq(x), e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+// v of lane i (the same i in all lanes).
+__device__ __forceinline__ double lane_value(double v, int i) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), i),
+                            __builtin_amdgcn_readlane(__double2loint(v), i));
+}
 
 __device__ inline double wave_sum(double v) {
+    v = row16_sum(v);
+    double s = 0.0;
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    return v;
+    for (int r = 0; r < 4; ++r) s += lane_value(v, 16 * r);
+    return s;
 }
 
 // Sums cnt (<= kChunk) per-thread values over the work-group into out[0..cnt)
@@ -82,15 +106,12 @@ __device__ inline void block_sums(const double (&v)[kChunk], int cnt, double *re
     __syncthreads();
     if (threadIdx.x < cnt) {
         const int c = threadIdx.x;
-        out[c] = ((red[c] + red[kChunk + c]) + red[2 * kChunk + c]) + red[3 * kChunk + c];
+        double t = red[c];
+#pragma unroll
+        for (int w = 1; w < kBoWaves; ++w) t += red[w * kChunk + c];
+        out[c] = t;
     }
     __syncthreads();
-}
-
-__device__ inline double block_sum1(double v, double *red, double *out) {
-    double a[kChunk] = {v};
-    block_sums(a, 1, red, out);
-    return out[0];
 }
 
 // T or (T + c)^-1 applied to the pair (u, v) (v may be null), out to (ou, ov);
@@ -152,147 +173,366 @@ __device__ void spectral_pair(const BoArgs &A, const double *u, const double *v,
     __syncthreads();
 }
 
-// Appends candidate `src` to the orthonormal columns Z[0..cnt) by classical
-// Gram-Schmidt twice; returns the new count (cnt + 1, or cnt if the
-// candidate was (numerically) in their span).
-template <int LOG2N>
-__device__ int append_orthonormal(double *Z, int cnt, const double *src, double *red, double *dots) {
-    constexpr int n = 1 << LOG2N;
-    constexpr int per = n / kBoThreads > 0 ? n / kBoThreads : 1;
-    const int tid = threadIdx.x;
-    double *z = Z + (size_t)cnt * n;
-    for (int e = tid; e < n; e += kBoThreads) z[e] = src[e];
-    __syncthreads();
-    double acc = 0.0;
-    for (int e = tid; e < n; e += kBoThreads) acc += z[e] * z[e];
-    const double n0 = sqrt(block_sum1(acc, red, dots + kBoMaxZ));
-    if (!(n0 > 0.0) || !isfinite(n0)) return cnt;
-    for (int pass = 0; pass < 2; ++pass) {
-        for (int c0 = 0; c0 < cnt; c0 += kChunk) {
-            const int cc = min(kChunk, cnt - c0);
-            double part[kChunk] = {0, 0, 0, 0, 0, 0, 0, 0};
-            for (int e = tid; e < n; e += kBoThreads) {
-                const double ze = z[e];
-#pragma unroll
-                for (int q = 0; q < kChunk; ++q)
-                    if (q < cc) part[q] += Z[(size_t)(c0 + q) * n + e] * ze;
-            }
-            block_sums(part, cc, red, dots + c0);
-        }
-        for (int e = tid; e < n; e += kBoThreads) {
-            double ze = z[e];
-            for (int i = 0; i < cnt; ++i) ze -= dots[i] * Z[(size_t)i * n + e];
-            z[e] = ze;
-        }
-        __syncthreads();
-    }
-    (void)per;
-    acc = 0.0;
-    for (int e = tid; e < n; e += kBoThreads) acc += z[e] * z[e];
-    const double n1 = sqrt(block_sum1(acc, red, dots + kBoMaxZ));
-    if (!(n1 > 1e-10 * n0) || !isfinite(n1)) return cnt;
-    const double inv = 1.0 / n1;
-    for (int e = tid; e < n; e += kBoThreads) z[e] *= inv;
-    __syncthreads();
-    return cnt + 1;
+// Place of entry i of a wave's transform buffer: one pad per 8 entries keeps
+// the exchanges of all passes (nearly) free of bank conflicts.
+__device__ inline int fft_at(int i) { return i + (i >> 3); }
+
+// Between the LDS writes of a wave and its other lanes' reads of them.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
-// Eigen-decomposition of the symmetric k x k matrix G (LDS, row-major, k <=
-// kBoMaxZ) by cyclic Jacobi: G -> diag(theta) ascending, Y the eigenvectors
-// (columns).  Round-robin ordering: in each of K - 1 rounds (K = k rounded up
-// to even) the K / 2 disjoint pairs rotate at once; player K - 1 stays, the
-// others turn.
-__device__ void jacobi(double *G, double *Y, int k, double *theta, double *red, double *scratch) {
-    const int tid = threadIdx.x;
-    __shared__ double cs[kBoMaxZ / 2], sn[kBoMaxZ / 2];
-    __shared__ int pp[kBoMaxZ / 2], qq[kBoMaxZ / 2];
-    for (int idx = tid; idx < k * k; idx += kBoThreads) Y[idx] = (idx / k == idx % k) ? 1.0 : 0.0;
-    __syncthreads();
-    const int K = (k + 1) & ~1, np = K / 2;
-    for (int sweep = 0; sweep < 40; ++sweep) {
-        double off = 0.0, dg = 0.0;
-        for (int idx = tid; idx < k * k; idx += kBoThreads) {
-            const double g = G[idx];
-            if (idx / k == idx % k) dg += g * g;
-            else off += g * g;
+// RADIX = 2, 4 or 8 points per butterfly: log2 RADIX radix-2 stages in
+// registers, on blocks of `len` points, elements len / RADIX apart.  Forward:
+// decimation in frequency; back: the same stages, conjugated, in reverse.
+template <int LOG2N, int RADIX, bool BACK>
+__device__ __forceinline__ void wave_pass(double2 *fb, const double2 *tw, int log2len, int lane) {
+    constexpr int n = 1 << LOG2N, LR = RADIX == 8 ? 3 : RADIX == 4 ? 2 : 1, BF = n / RADIX;
+    const int lsub = log2len - LR;                   // log2 of the element distance
+#pragma unroll
+    for (int b0 = 0; b0 < BF; b0 += 64) {
+        const int b = b0 + lane;
+        if (BF < 64 && b >= BF) break;
+        const int j = b & ((1 << lsub) - 1), base = ((b >> lsub) << log2len) + j;
+        double2 x[RADIX];
+#pragma unroll
+        for (int q = 0; q < RADIX; ++q) x[q] = fb[fft_at(base + (q << lsub))];
+#pragma unroll
+        for (int t = 0; t < LR; ++t) {
+            const int st = BACK ? LR - 1 - t : t;    // stage: distance RADIX >> (st + 1) elements
+            const int dist = RADIX >> (st + 1);
+#pragma unroll
+            for (int q = 0; q < RADIX; ++q) {
+                if (q & dist) continue;
+                // exp(-2 pi i pos / (len >> st)), pos the place in the half block
+                const int pos = j + ((q & (dist - 1)) << lsub);
+                const double2 w = tw[pos << (LOG2N - log2len + st)];
+                const double2 u = x[q], v = x[q + dist];
+                if (!BACK) {
+                    x[q] = cadd(u, v);
+                    x[q + dist] = cmul(csub(u, v), w);
+                } else {
+                    const double2 z = cmulc(w, v);
+                    x[q] = cadd(u, z);
+                    x[q + dist] = csub(u, z);
+                }
+            }
         }
-        double two[kChunk] = {off, dg};
-        block_sums(two, 2, red, scratch);
-        if (!(scratch[0] > 1e-30 * scratch[1])) break;
-        for (int r = 0; r < K - 1; ++r) {
-            if (tid < np) {
-                int p, q;
-                if (tid == 0) {
-                    p = r;
-                    q = K - 1;
-                } else {
-                    p = (r + tid) % (K - 1);
-                    q = (r - tid + K - 1) % (K - 1);
-                }
-                double c = 1.0, s = 0.0;
-                if (p < k && q < k) {
-                    const double apq = G[p * k + q];
-                    if (fabs(apq) > 1e-300) {
-                        const double tau = (G[q * k + q] - G[p * k + p]) / (2.0 * apq);
-                        double t;
-                        if (fabs(tau) > 1e150) t = 0.5 / tau;
-                        else t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-                        c = 1.0 / sqrt(1.0 + t * t);
-                        s = t * c;
-                    }
-                } else {
-                    p = q = 0;
-                }
-                pp[tid] = p;
-                qq[tid] = q;
-                cs[tid] = c;
-                sn[tid] = s;
-            }
-            __syncthreads();
-            // rows p, q of G <- J^T G
-            for (int idx = tid; idx < np * k; idx += kBoThreads) {
-                const int pr = idx / k, col = idx - pr * k;
-                const double c = cs[pr], s = sn[pr];
-                if (s == 0.0) continue;
-                const int p = pp[pr], q = qq[pr];
-                const double gp = G[p * k + col], gq = G[q * k + col];
-                G[p * k + col] = c * gp - s * gq;
-                G[q * k + col] = s * gp + c * gq;
-            }
-            __syncthreads();
-            // columns p, q of G <- G J and of Y <- Y J
-            for (int idx = tid; idx < np * k; idx += kBoThreads) {
-                const int pr = idx / k, row = idx - pr * k;
-                const double c = cs[pr], s = sn[pr];
-                if (s == 0.0) continue;
-                const int p = pp[pr], q = qq[pr];
-                const double gp = G[row * k + p], gq = G[row * k + q];
-                G[row * k + p] = c * gp - s * gq;
-                G[row * k + q] = s * gp + c * gq;
-                const double yp = Y[row * k + p], yq = Y[row * k + q];
-                Y[row * k + p] = c * yp - s * yq;
-                Y[row * k + q] = s * yp + c * yq;
-            }
-            __syncthreads();
+#pragma unroll
+        for (int q = 0; q < RADIX; ++q) fb[fft_at(base + (q << lsub))] = x[q];
+    }
+    wave_sync();
+}
+
+// As spectral_pair, by one wave on its own buffer: in-order LDS, no barrier.
+template <int LOG2N>
+__device__ void spectral_wave(const BoArgs &A, const double *u, const double *v, double *ou, double *ov,
+                              const double *V, bool hamiltonian, double c, double2 *fb, const double2 *tw) {
+    constexpr int n = 1 << LOG2N, R0 = LOG2N % 3 == 0 ? 3 : LOG2N % 3;   // stages of the last pass forward
+    const int lane = threadIdx.x & 63;
+    for (int e = lane; e < n; e += 64) fb[fft_at(e)] = make_double2(u[e], v ? v[e] : 0.0);
+    wave_sync();
+#pragma unroll 1
+    for (int l = LOG2N; l > R0; l -= 3) wave_pass<LOG2N, 8, false>(fb, tw, l, lane);
+    wave_pass<LOG2N, 1 << R0, false>(fb, tw, R0, lane);
+    for (int p = lane; p < n; p += 64) {
+        const double k = A.kin[(int)(__brev((unsigned)p) >> (32 - LOG2N))];
+        fb[fft_at(p)] = cscale(fb[fft_at(p)], hamiltonian ? k : 1.0 / (k + c));
+    }
+    wave_sync();
+    wave_pass<LOG2N, 1 << R0, true>(fb, tw, R0, lane);
+#pragma unroll 1
+    for (int l = R0 + 3; l <= LOG2N; l += 3) wave_pass<LOG2N, 8, true>(fb, tw, l, lane);
+    const double inv = 1.0 / n;
+    for (int e = lane; e < n; e += 64) {
+        const double2 y = fb[fft_at(e)];
+        double yu = y.x * inv, yv = y.y * inv;
+        if (hamiltonian) {
+            yu += V[e] * u[e];
+            if (v) yv += V[e] * v[e];
+        }
+        ou[e] = yu;
+        if (v) ov[e] = yv;
+    }
+    wave_sync();
+}
+
+// Waves with a transform buffer: all, but for 1024 points, where eight buffers
+// are more LDS than there is.
+constexpr int fft_waves(int log2n) { return log2n < 10 ? kBoWaves : 4; }
+
+// h_e or the preconditioner on `cols` columns of `in`, to `out`.
+template <int LOG2N>
+__device__ void apply_columns(const BoArgs &A, const double *in, double *out, int cols, const double *V,
+                              bool hamiltonian, double c, double2 *fb, const double2 *tw) {
+    constexpr int n = 1 << LOG2N;
+    if constexpr (LOG2N <= 10) {
+        const int wave = threadIdx.x >> 6;
+        for (int q = wave < fft_waves(LOG2N) ? 2 * wave : cols; q < cols; q += 2 * fft_waves(LOG2N)) {
+            const bool two = q + 1 < cols;
+            const double *u = in + (size_t)q * n;
+            double *ou = out + (size_t)q * n;
+            spectral_wave<LOG2N>(A, u, two ? u + n : nullptr, ou, two ? ou + n : nullptr, V, hamiltonian, c,
+                                 fb + wave * fft_at(n), tw);
+        }
+        __syncthreads();
+    } else {
+        for (int q = 0; q < cols; q += 2) {
+            const bool two = q + 1 < cols;
+            const double *u = in + (size_t)q * n;
+            double *ou = out + (size_t)q * n;
+            spectral_pair<LOG2N>(A, u, two ? u + n : nullptr, ou, two ? ou + n : nullptr, V, hamiltonian, c, fb);
         }
     }
-    if (tid == 0) {
-        for (int a = 0; a < k; ++a) theta[a] = G[a * k + a];
-        // ascending order (selection sort, columns of Y follow)
-        for (int a = 0; a < k; ++a) {
-            int best = a;
-            for (int b = a + 1; b < k; ++b)
-                if (theta[b] < theta[best]) best = b;
-            if (best != a) {
-                const double t = theta[a];
-                theta[a] = theta[best];
-                theta[best] = t;
-                for (int row = 0; row < k; ++row) {
-                    const double y = Y[row * k + a];
-                    Y[row * k + a] = Y[row * k + best];
-                    Y[row * k + best] = y;
-                }
+}
+
+typedef double dbl4 __attribute__((ext_vector_type(4)));
+
+// G[a][b] = x_a . y_b for the first k columns of X and Y (a <= b computed,
+// mirrored), by matrix products: 16 x 16 tiles of (a, b), the grid points the
+// reduction, in steps of 8 taken by the waves in turn; part: 256 doubles a wave.
+template <int LOG2N>
+__device__ void gram(const double *X, const double *Y, int k, double *G, double (*part)[256]) {
+    constexpr int n = 1 << LOG2N;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, row = lane & 15, quarter = lane >> 4;
+    for (int a0 = 0; a0 < k; a0 += 16)
+        for (int b0 = a0; b0 < k; b0 += 16) {
+            const double *x = X + (size_t)min(a0 + row, k - 1) * n + 2 * quarter;
+            const double *y = Y + (size_t)min(b0 + row, k - 1) * n + 2 * quarter;
+            dbl4 acc = {0, 0, 0, 0};
+#pragma unroll 4
+            for (int e = 8 * wave; e < n; e += 8 * kBoWaves) {
+                const double2 xe = *reinterpret_cast<const double2 *>(x + e), ye = *reinterpret_cast<const double2 *>(y + e);
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xe.x, ye.x, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xe.y, ye.y, acc, 0, 0, 0);
             }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) part[wave][16 * mfma_row_f64(lane, v) + row] = acc[v];
+            __syncthreads();
+            const int a = a0 + (tid >> 4), b = b0 + (tid & 15);
+            if (tid < 256 && a < k && b < k && a <= b) {
+                double g = part[0][tid];
+#pragma unroll
+                for (int w = 1; w < kBoWaves; ++w) g += part[w][tid];
+                G[a * k + b] = g;
+                G[b * k + a] = g;
+            }
+            __syncthreads();
+        }
+}
+
+// Orthonormalises the first k columns of Z in place, in their order (at most
+// MZ of them); returns how many are left.
+template <int LOG2N, int MZ>
+__device__ int orthonormalise(double *Z, int k, double *M, double (*part)[256], double *scl, int *pos) {
+    constexpr int n = 1 << LOG2N;
+    const int tid = threadIdx.x;
+    for (int pass = 0; pass < 2; ++pass) {
+        gram<LOG2N>(Z, Z, k, M, part);
+        if (tid < 64) {
+            // Cholesky by one wave, column `lane` of the matrix in a lane's
+            // registers.  Unit columns first (scl; 0 drops a zero or non-finite
+            // one); column j of R in row j of M, 1 / R_jj on the diagonal; pos:
+            // place of a column, -1: dropped, its row and column zeros.
+            const int lane = tid;
+            double col[MZ];
+#pragma unroll
+            for (int i = 0; i < MZ; ++i) col[i] = i < k && lane < k ? M[i * k + lane] : 0.0;
+            double mine = 0.0;
+#pragma unroll
+            for (int i = 0; i < MZ; ++i) mine = lane == i ? col[i] : mine;
+            mine = mine > 1e-290 && isfinite(mine) ? inverse_root(mine) : 0.0;
+#pragma unroll
+            for (int i = 0; i < MZ; ++i) col[i] *= mine * lane_value(mine, i);
+            int kept = 0, place = -1;
+#pragma unroll
+            for (int j = 0; j < MZ; ++j) {
+                const double d = lane_value(col[j], j);
+                // a column kept before has nearly all of its norm left
+                const bool keep = d > (pass ? 0.1 : 1e-14);
+                const double inv = keep ? inverse_root(d) : 0.0;
+                col[j] = keep ? col[j] * inv : 0.0;  // (it may be NaN)
+#pragma unroll
+                for (int i = j + 1; i < MZ; ++i) col[i] -= lane_value(col[j], i) * col[j];
+                if (lane == j) {
+                    place = keep ? kept : -1;
+                    col[j] = inv;
+                }
+                kept += keep;
+            }
+#pragma unroll
+            for (int i = 0; i < MZ; ++i)
+                if (i <= lane && lane < MZ) M[lane * MZ + i] = place < 0 ? 0.0 : col[i];
+            if (lane < MZ) {
+                scl[lane] = mine;
+                pos[lane] = place;
+            }
+            if (lane == 0) pos[MZ] = kept;
+        }
+        __syncthreads();
+        // Z <- Z R^-1, element by element: z_j = (c_j - sum_{i<j} R_ij z_i) / R_jj
+        for (int e = tid; e < n; e += kBoThreads) {
+            double z[MZ];
+#pragma unroll
+            for (int j = 0; j < MZ; ++j) {
+                const double f = scl[j];
+                z[j] = j < k ? Z[(size_t)j * n + e] : 0.0;
+                z[j] = f != 0.0 ? f * z[j] : 0.0;
+            }
+#pragma unroll
+            for (int j = 0; j < MZ; ++j) {
+                double x = z[j];
+#pragma unroll
+                for (int i = 0; i < j; ++i) x -= M[j * MZ + i] * z[i];
+                z[j] = x * M[j * MZ + j];
+                // here and now: not sunk to the store, with R kept for it in scratch
+                asm volatile("" : "+v"(z[j])::"memory");
+            }
+#pragma unroll
+            for (int j = 0; j < MZ; ++j) {
+                const int at = __builtin_amdgcn_readfirstlane(pos[j]);
+                if (at >= 0) Z[(size_t)at * n + e] = z[j];
+            }
+        }
+        __syncthreads();
+        k = pos[MZ];
+        __syncthreads();
+    }
+    return k;
+}
+
+// The rotation (c, s) that clears b / 2 between diagonal entries g_p and g_q = g_p + d,
+// of at most pi / 4: cos 2t = |d| / h, h = |(d, b)|; c = sqrt((1 + cos 2t) / 2),
+// s = sign(d) b / (2 h c).
+__device__ __forceinline__ double2 rotation(double d, double b) {
+    const double big = fmax(fabs(d), fabs(b));
+    const int sc = -__builtin_amdgcn_frexp_exp(big);
+    const double dn = ldexp(d, sc), bn = ldexp(b, sc);
+    const double ih = inverse_root(dn * dn + bn * bn), c2 = 0.5 * (1.0 + fabs(dn) * ih), ic = inverse_root(c2);
+    const bool turn = big > 1e-300;
+    return make_double2(turn ? c2 * ic : 1.0, turn ? copysign(0.5 * ih * ic, d) * bn : 0.0);
+}
+
+// Eigen-decomposition of the symmetric k x k matrix G (LDS, row-major, k <= MZ)
+// by cyclic Jacobi: theta ascending, Y the eigenvectors (columns).  Round-robin
+// ordering: in each of K - 1 rounds (K = k rounded up to even) K / 2 disjoint
+// pairs rotate at once; one player stays, the others turn.  S holds the matrix
+// in seats, pair i in rows and columns 2 i and 2 i + 1: a lane rotates the 2 x 2
+// block of two pairs from both sides and puts the results where the next round
+// seats them, and the same for the rows of T, the vectors.  A sweep brings all
+// back to their first seats.
+// A round is two phases, the rotations and the blocks.  Up to 16 columns one
+// wave does all, a block and two rows of a pair per lane, without a barrier;
+// larger ones take the whole work-group.
+// Seat strides are padded against bank conflicts.
+template <int MZ>
+__device__ void jacobi(double *G, double *Y, int k, double *theta, double *S) {
+    constexpr int KP = (MZ + 1) & ~1, NP = KP / 2, LD = KP + 2;
+    constexpr bool kWave = NP <= 8;
+    constexpr int GB = kWave ? 1 : (NP * NP + kBoThreads - 1) / kBoThreads, STEP = kWave ? 64 : kBoThreads;
+    constexpr int YB = (NP * KP + STEP - 1) / STEP;
+    const int tid = threadIdx.x;
+    double *T = S + KP * LD;
+    __shared__ double2 cs[NP];
+    const int K = (k + 1) & ~1, np = K / 2;
+    auto fence = [] {
+        if (kWave) wave_sync();
+        else __syncthreads();
+    };
+    auto next = [&](int seat) {
+        const int i = seat >> 1;
+        if (np == 1 || seat == 0 || seat >= K) return seat;
+        if (seat & 1) return i ? seat - 2 : 2;
+        return i == np - 1 ? seat + 1 : seat + 2;
+    };
+    if (!kWave || tid < 64) {
+        for (int idx = tid; idx < KP * KP; idx += STEP) {
+            const int a = idx / KP, b = idx % KP;
+            S[a * LD + b] = a < k && b < k ? G[a * k + b] : 0.0;
+            T[a * LD + b] = a == b ? 1.0 : 0.0;
+        }
+        // blocks (gi, gj), rows yr of pair yi; unused ones turn seats of zeros
+        int gi[GB], gj[GB], yi[YB], yr[YB];
+#pragma unroll
+        for (int q = 0; q < GB; ++q) {
+            const int idx = tid + q * STEP;
+            gi[q] = idx < NP * NP ? idx / NP : -1;
+            gj[q] = idx % NP;
+        }
+#pragma unroll
+        for (int q = 0; q < YB; ++q) {
+            const int idx = tid + q * STEP;
+            yi[q] = idx < NP * KP ? idx % NP : -1;
+            yr[q] = idx / NP;
+        }
+        fence();
+        for (int sweep = 0; sweep < 40; ++sweep) {
+            double off = 0.0, dg = 0.0;              // (every wave for itself)
+            for (int idx = tid & 63; idx < KP * KP; idx += 64) {
+                const int a = idx / KP, b = idx % KP;
+                const double g = S[a * LD + b];
+                if (a == b) dg += g * g;
+                else off += g * g;
+            }
+            off = wave_sum(off);
+            dg = wave_sum(dg);
+            if (!(off > 1e-30 * dg)) break;
+            for (int r = 0; r < K - 1; ++r) {
+                double2 bp[GB], bq[GB], y[YB];
+                double2 turn;
+                if (kWave || tid < NP) {
+                    const int at = 2 * (kWave ? tid % NP : tid);
+                    const double2 p = *reinterpret_cast<const double2 *>(S + at * (LD + 1));
+                    turn = rotation(S[(at + 1) * (LD + 1)] - p.x, 2.0 * p.y);
+                    cs[at / 2] = turn;
+                }
+#pragma unroll
+                for (int q = 0; q < GB; ++q) {
+                    if (!kWave && gi[q] < 0) continue;
+                    bp[q] = *reinterpret_cast<const double2 *>(S + 2 * gi[q] * LD + 2 * gj[q]);
+                    bq[q] = *reinterpret_cast<const double2 *>(S + (2 * gi[q] + 1) * LD + 2 * gj[q]);
+                }
+#pragma unroll
+                for (int q = 0; q < YB; ++q) {
+                    if (!kWave && yi[q] < 0) continue;
+                    y[q] = *reinterpret_cast<const double2 *>(T + yr[q] * LD + 2 * yi[q]);
+                }
+                fence();
+#pragma unroll
+                for (int q = 0; q < GB; ++q) {
+                    if (!kWave && gi[q] < 0) continue;
+                    const double2 f = cs[gi[q]], g = kWave ? turn : cs[gj[q]];
+                    const double2 hp = make_double2(f.x * bp[q].x - f.y * bq[q].x, f.x * bp[q].y - f.y * bq[q].y);
+                    const double2 hq = make_double2(f.y * bp[q].x + f.x * bq[q].x, f.y * bp[q].y + f.x * bq[q].y);
+                    const int i = next(2 * gi[q]) * LD, i1 = next(2 * gi[q] + 1) * LD;
+                    const int j = next(2 * gj[q]), j1 = next(2 * gj[q] + 1);
+                    S[i + j] = g.x * hp.x - g.y * hp.y;
+                    S[i + j1] = g.y * hp.x + g.x * hp.y;
+                    S[i1 + j] = g.x * hq.x - g.y * hq.y;
+                    S[i1 + j1] = g.y * hq.x + g.x * hq.y;
+                }
+#pragma unroll
+                for (int q = 0; q < YB; ++q) {
+                    if (!kWave && yi[q] < 0) continue;
+                    const double2 f = kWave ? turn : cs[yi[q]];
+                    T[yr[q] * LD + next(2 * yi[q])] = f.x * y[q].x - f.y * y[q].y;
+                    T[yr[q] * LD + next(2 * yi[q] + 1)] = f.y * y[q].x + f.x * y[q].y;
+                }
+                fence();
+            }
+        }
+        // ascending order: each column to the place its eigenvalue ranks at
+        for (int idx = tid; idx < k * k; idx += STEP) {
+            const int row = idx / k, a = idx % k;
+            const double e = S[a * LD + a];
+            int at = 0;
+            for (int b = 0; b < k; ++b) {
+                const double o = S[b * LD + b];
+                at += o < e || (o == e && b < a);
+            }
+            Y[row * k + at] = T[row * LD + a];
+            if (row == 0) theta[at] = e;
         }
     }
     __syncthreads();
@@ -307,25 +547,33 @@ __device__ inline double unit_hash(unsigned long long x) {
     return (double)(x >> 11) * (2.0 / 9007199254740992.0) - 1.0;
 }
 
-template <int LOG2N>
-__global__ void __launch_bounds__(kBoThreads) k_bo_lobpcg(BoArgs A) {
+// MZ: most columns of the basis (3 m), 15 (up to three states) or 36.
+template <int LOG2N, int MZ>
+__global__ void __launch_bounds__(kBoThreads, MZ <= 15 ? 2 : 1) k_bo_lobpcg(BoArgs A) {
     constexpr int n = 1 << LOG2N;
-    __shared__ double2 fb[n];
+    constexpr int kTransform = LOG2N <= 10 ? fft_waves(LOG2N) * (n + n / 8) : n;
+    constexpr int kTwiddles = LOG2N <= 10 ? n / 2 : 1;
+    __shared__ double2 fb[kTransform];
+    __shared__ double2 tw[kTwiddles];
     __shared__ double red[kBoWaves * kChunk];
-    __shared__ double dots[kBoMaxZ + 8];
-    __shared__ double G[kBoMaxZ * kBoMaxZ];
-    __shared__ double Y[kBoMaxZ * kBoMaxZ];
-    __shared__ double theta[kBoMaxZ];
+    __shared__ double dots[kChunk];
+    __shared__ double G[MZ * MZ];
+    __shared__ double Y[MZ * MZ];
+    __shared__ double theta[MZ], scl[MZ];
+    __shared__ double2 seats2[((MZ + 1) & ~1) * (((MZ + 1) & ~1) + 2)];   // two matrices
+    double *seats = reinterpret_cast<double *>(seats2);
+    __shared__ int pos[MZ + 1];
     __shared__ double scratch[kChunk];
+    __shared__ double2 part2[kBoWaves][128];
+    double (*part)[256] = reinterpret_cast<double (*)[256]>(part2);
     const int j = blockIdx.x, tid = threadIdx.x, m = A.m;
     double *V = A.ws + (size_t)j * A.ws_stride;
     double *Z = V + n;
     double *HZ = Z + (size_t)kBoMaxZ * n;
-    double *X = HZ + (size_t)kBoMaxZ * n;
-    double *P = X + (size_t)kBoMaxBlock * n;
-    double *Wr = P + (size_t)kBoMaxBlock * n;
     const double Rj = A.Rv[j];
 
+    if (LOG2N <= 10)
+        for (int e = tid; e < kTwiddles; e += kBoThreads) tw[e] = A.tw[e];
     // the clamped potential and its range on the grid
     double vmin = INFINITY, vmax = -INFINITY;
     bool finite = true;
@@ -375,91 +623,58 @@ __global__ void __launch_bounds__(kBoThreads) k_bo_lobpcg(BoArgs A) {
     // starting block: pseudo-random columns, smoothed by the preconditioner
     for (int c = 0; c < m; ++c)
         for (int e = tid; e < n; e += kBoThreads)
-            Wr[(size_t)c * n + e] = unit_hash(((unsigned long long)j << 40) ^ ((unsigned long long)c << 20) ^ e);
+            Z[(size_t)c * n + e] = unit_hash(((unsigned long long)j << 40) ^ ((unsigned long long)c << 20) ^ e);
     __syncthreads();
-    for (int c = 0; c < m; c += 2) {
-        double *u = Wr + (size_t)c * n, *v = c + 1 < m ? u + n : nullptr;
-        spectral_pair<LOG2N>(A, u, v, u, v, V, false, cshift, fb);
-    }
-    int kz = 0;
-    for (int c = 0; c < m; ++c) kz = append_orthonormal<LOG2N>(Z, kz, Wr + (size_t)c * n, red, dots);
+    apply_columns<LOG2N>(A, Z, Z, m, V, false, cshift, fb, tw);
+    int kz = orthonormalise<LOG2N, MZ>(Z, m, G, part, scl, pos);
 
     int it = 0;
     double worst = INFINITY;
     for (;; ++it) {
-        // h_e on the whole basis, afresh
-        for (int c = 0; c < kz; c += 2) {
-            const double *u = Z + (size_t)c * n, *v = c + 1 < kz ? u + n : nullptr;
-            spectral_pair<LOG2N>(A, u, v, HZ + (size_t)c * n, v ? HZ + (size_t)(c + 1) * n : nullptr, V, true,
-                                 cshift, fb);
-        }
-        // projected matrix G[a][b] = z_a . (h_e z_b), upper part, mirrored
-        for (int a = 0; a < kz; ++a) {
-            for (int b0 = a; b0 < kz; b0 += kChunk) {
-                const int cc = min(kChunk, kz - b0);
-                double part[kChunk] = {0, 0, 0, 0, 0, 0, 0, 0};
-                for (int e = tid; e < n; e += kBoThreads) {
-                    const double za = Z[(size_t)a * n + e];
-#pragma unroll
-                    for (int q = 0; q < kChunk; ++q)
-                        if (q < cc) part[q] += za * HZ[(size_t)(b0 + q) * n + e];
-                }
-                block_sums(part, cc, red, dots);
-                if (tid < cc) {
-                    G[a * kz + b0 + tid] = dots[tid];
-                    G[(b0 + tid) * kz + a] = dots[tid];
-                }
-                __syncthreads();
-            }
-        }
-        jacobi(G, Y, kz, theta, red, scratch);
+        // h_e on the whole basis, afresh, and the projected matrix
+        apply_columns<LOG2N>(A, Z, HZ, kz, V, true, cshift, fb, tw);
+        gram<LOG2N>(Z, HZ, kz, G, part);
+        jacobi<MZ>(G, Y, kz, theta, seats);
         const int mk = min(m, kz);
-        // Ritz block, its residuals and the new directions
+        // in place of the basis: the Ritz block, its residuals, the new
+        // directions (an element's columns are one thread's)
+        const int cw = min(A.nwant, mk);
+        double rr[kChunk] = {0, 0, 0, 0, 0, 0, 0, 0};
         for (int e = tid; e < n; e += kBoThreads) {
+            double z[MZ], hz[MZ];
+#pragma unroll
+            for (int a = 0; a < MZ; ++a) {
+                z[a] = a < kz ? Z[(size_t)a * n + e] : 0.0;
+                hz[a] = a < kz ? HZ[(size_t)a * n + e] : 0.0;
+            }
             for (int i = 0; i < mk; ++i) {
                 double x = 0.0, hx = 0.0, p = 0.0;
-                for (int a = 0; a < kz; ++a) {
-                    const double y = Y[a * kz + i];
-                    const double za = Z[(size_t)a * n + e];
-                    x += za * y;
-                    hx += HZ[(size_t)a * n + e] * y;
-                    if (a >= m) p += za * y;
+#pragma unroll
+                for (int a = 0; a < MZ; ++a) {
+                    const double y = a < kz ? Y[a * kz + i] : 0.0;
+                    x += z[a] * y;
+                    hx += hz[a] * y;
+                    if (a >= m) p += z[a] * y;
                 }
-                X[(size_t)i * n + e] = x;
-                Wr[(size_t)i * n + e] = hx - theta[i] * x;
-                P[(size_t)i * n + e] = p;
-            }
-        }
-        __syncthreads();
-        worst = 0.0;
-        {
-            double part[kChunk] = {0, 0, 0, 0, 0, 0, 0, 0};
-            const int cw = min(A.nwant, mk);
-            for (int e = tid; e < n; e += kBoThreads) {
+                const double w = hx - theta[i] * x;
+                Z[(size_t)i * n + e] = x;
+                Z[(size_t)(mk + i) * n + e] = w;
+                Z[(size_t)(2 * mk + i) * n + e] = p;
 #pragma unroll
                 for (int q = 0; q < kChunk; ++q)
-                    if (q < cw) {
-                        const double r = Wr[(size_t)q * n + e];
-                        part[q] += r * r;
-                    }
+                    if (q == i && q < cw) rr[q] += w * w;
             }
-            block_sums(part, cw, red, dots);
-            for (int q = 0; q < cw; ++q) worst = fmax(worst, sqrt(dots[q]));
-            __syncthreads();
         }
+        block_sums(rr, cw, red, dots);
+        worst = 0.0;
+        for (int q = 0; q < cw; ++q) worst = fmax(worst, sqrt(dots[q]));
+        __syncthreads();
         if (!(worst > A.tol) || it + 1 >= A.max_iter || !isfinite(worst)) break;
-        // preconditioned residuals
-        for (int c = 0; c < mk; c += 2) {
-            double *u = Wr + (size_t)c * n, *v = c + 1 < mk ? u + n : nullptr;
-            spectral_pair<LOG2N>(A, u, v, u, v, V, false, cshift, fb);
-        }
         // new basis: the Ritz block, the preconditioned residuals, the directions
-        kz = 0;
-        for (int c = 0; c < mk; ++c) kz = append_orthonormal<LOG2N>(Z, kz, X + (size_t)c * n, red, dots);
-        for (int c = 0; c < mk; ++c) kz = append_orthonormal<LOG2N>(Z, kz, Wr + (size_t)c * n, red, dots);
-        if (it > 0)
-            for (int c = 0; c < mk; ++c) kz = append_orthonormal<LOG2N>(Z, kz, P + (size_t)c * n, red, dots);
+        apply_columns<LOG2N>(A, Z + (size_t)mk * n, Z + (size_t)mk * n, mk, V, false, cshift, fb, tw);
+        kz = orthonormalise<LOG2N, MZ>(Z, it > 0 ? 3 * mk : 2 * mk, G, part, scl, pos);
     }
+    const double *X = Z;
 
     // output: grid normalisation, largest-magnitude entry positive
     const double scale = 1.0 / sqrt(A.h);
@@ -517,7 +732,9 @@ __global__ void __launch_bounds__(kBoThreads) k_bo_lobpcg(BoArgs A) {
 
 template <int LOG2N>
 void launch_bo_t(const BoArgs &a, int nv, hipStream_t s) {
-    hipLaunchKernelGGL(k_bo_lobpcg<LOG2N>, dim3(nv), dim3(kBoThreads), 0, s, a);
+    // the registers of a column set follow its size: 15 up to three states
+    const auto kernel = 3 * a.m <= 15 ? k_bo_lobpcg<LOG2N, 15> : k_bo_lobpcg<LOG2N, kBoMaxZ>;
+    hipLaunchKernelGGL(kernel, dim3(nv), dim3(kBoThreads), 0, s, a);
 }
 
 }  // namespace
