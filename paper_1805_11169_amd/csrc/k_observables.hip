@@ -21,93 +21,84 @@ __device__ inline dbl4 mfma(double a, double b, dbl4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// Psi = U^T V, U[a][i] = C_a psi1[a][i], V[a][j] = psi2[a][j], a < Np.  One
-// 64 x 64 tile of Psi per work-group of 4 waves, wave w on the 32 x 32
-// quarter (rows 32 (w / 2), columns 32 (w % 2)) as 2 x 2 fragments of
-// v_mfma_f64_16x16x4 with rows = i, columns = j and the trajectory a as the
-// reduction index.  16-trajectory chunks of U (times C_a) and V are staged
-// through double-buffered LDS by coalesced row loads (64 consecutive grid
-// points per row).  Rows or columns beyond the grid (n = 32) read zeros and
-// are not stored.
-constexpr int kOT = 64, kOKC = 16, kOLD = kOT + 1;
-
-__global__ void __launch_bounds__(256) k_obs_psi(const double2 *__restrict__ psi1, const double2 *__restrict__ psi2,
-                                                 const double2 *__restrict__ C, int nr, int nR, int Np,
-                                                 double2 *__restrict__ Psi) {
-    __shared__ double2 sU[2][kOKC][kOLD];
-    __shared__ double2 sV[2][kOKC][kOLD];
+// Psi = U^T V, U[a][i] = C_a psi1[a][i], V[a][j] = psi2[a][j], a < Np.  A
+// work-group per 16 F x 16 F tile of Psi, F x F fragments of v_mfma_f64_16x16x4
+// with rows = i, columns = j and the trajectory a as the reduction index; its
+// four waves take the steps of the reduction (16 trajectories each) in turn,
+// operands straight from global memory (the 16 grid points of a fragment are
+// consecutive) one step ahead; the partial tiles meet in LDS and are added in
+// the order of the waves.  Bound by the reads of psi from L2 where the tiles
+// fill the device, by latency on small grids.  Against 64 x 64 tiles through
+// LDS, a wave to a quarter of the tile (32 work-groups on 512 x 256), whole
+// call: N = 1024 on 512 x 256, 276 -> 82 us; N = 2048 on 1024 x 256, 496 -> 138;
+// N = 1500 on 1024 x 512, 362 -> 180; N = 4096 on 4096 x 512, 1.44 -> 1.20 ms.
+template <int F>
+__global__ void __launch_bounds__(256) k_obs_psi(const double2 *__restrict__ psi1,
+                                                       const double2 *__restrict__ psi2,
+                                                       const double2 *__restrict__ C, int nr, int nR, int Np,
+                                                       double2 *__restrict__ Psi) {
+    constexpr int T = 16 * F;
+    __shared__ double2 part[4][T * T];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int row = lane & 15, quarter = lane >> 4;
-    const int i0 = blockIdx.y * kOT, j0 = blockIdx.x * kOT;
-    const int wi = 32 * (wave >> 1), wj = 32 * (wave & 1);
-    // staging: thread t loads grid point c = t % 64 of the chunk rows t / 64 + 4 m
-    const int sc = t & 63, sr = t >> 6;
-    const bool ui = i0 + sc < nr, vj = j0 + sc < nR;
-    dbl4 re[2][2], im[2][2];
+    const int i0 = blockIdx.y * T, j0 = blockIdx.x * T;
+    dbl4 re[F][F], im[F][F];
 #pragma unroll
-    for (int f = 0; f < 2; ++f)
+    for (int f = 0; f < F; ++f)
 #pragma unroll
-        for (int g = 0; g < 2; ++g) {
+        for (int g = 0; g < F; ++g) {
             re[f][g] = dbl4{0, 0, 0, 0};
             im[f][g] = dbl4{0, 0, 0, 0};
         }
-    double2 ru[4], rv[4];
-    auto load = [&](int a0) {
+    const double2 *pu = psi1 + i0 + row, *pv = psi2 + j0 + row;
+    double2 c[4], u[4][F], v[4][F];
+    auto load = [&](int a0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const int a = a0 + sr + 4 * m;
-            ru[m] = ui ? cmul(C[a], psi1[(size_t)a * nr + i0 + sc]) : make_double2(0.0, 0.0);
-            rv[m] = vj ? psi2[(size_t)a * nR + j0 + sc] : make_double2(0.0, 0.0);
-        }
-    };
-    auto stage = [&](int buf) {
+        for (int s = 0; s < 4; ++s) {
+            const int a = a0 + 4 * s + quarter;
+            c[s] = C[a];
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            sU[buf][sr + 4 * m][sc] = ru[m];
-            sV[buf][sr + 4 * m][sc] = rv[m];
-        }
-    };
-    load(0);
-    stage(0);
-    __syncthreads();
-    const int nch = Np / kOKC;
-    for (int ch = 0; ch < nch; ++ch) {
-        const int buf = ch & 1;
-        const bool more = ch + 1 < nch;
-        if (more) load((ch + 1) * kOKC);
-#pragma unroll
-        for (int s4 = 0; s4 < kOKC / 4; ++s4) {
-            const int kk = 4 * s4 + quarter;
-            double2 uv[2], vv[2];
-#pragma unroll
-            for (int f = 0; f < 2; ++f) {
-                uv[f] = sU[buf][kk][wi + 16 * f + row];
-                vv[f] = sV[buf][kk][wj + 16 * f + row];
+            for (int f = 0; f < F; ++f) {
+                u[s][f] = pu[(size_t)a * nr + 16 * f];
+                v[s][f] = pv[(size_t)a * nR + 16 * f];
             }
-#pragma unroll
-            for (int f = 0; f < 2; ++f)
-#pragma unroll
-                for (int g = 0; g < 2; ++g) {
-                    // u v = (ur vr - ui vi) + i (ur vi + ui vr)
-                    re[f][g] = mfma(uv[f].x, vv[g].x, re[f][g]);
-                    re[f][g] = mfma(-uv[f].y, vv[g].y, re[f][g]);
-                    im[f][g] = mfma(uv[f].x, vv[g].y, im[f][g]);
-                    im[f][g] = mfma(uv[f].y, vv[g].x, im[f][g]);
-                }
         }
-        if (more) stage(buf ^ 1);
-        __syncthreads();
+    };
+    load(16 * wave);
+    for (int a0 = 16 * wave; a0 < Np; a0 += 64) {
+        double2 uc[4][F], vc[4][F];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int f = 0; f < F; ++f) {
+                uc[s][f] = cmul(c[s], u[s][f]);
+                vc[s][f] = v[s][f];
+            }
+        if (a0 + 64 < Np) load(a0 + 64);
+        pin_loads();
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int f = 0; f < F; ++f)
+#pragma unroll
+                for (int g = 0; g < F; ++g) {
+                    re[f][g] = mfma(uc[s][f].x, vc[s][g].x, re[f][g]);
+                    re[f][g] = mfma(-uc[s][f].y, vc[s][g].y, re[f][g]);
+                    im[f][g] = mfma(uc[s][f].x, vc[s][g].y, im[f][g]);
+                    im[f][g] = mfma(uc[s][f].y, vc[s][g].x, im[f][g]);
+                }
     }
 #pragma unroll
-    for (int f = 0; f < 2; ++f)
+    for (int f = 0; f < F; ++f)
 #pragma unroll
-        for (int g = 0; g < 2; ++g)
+        for (int g = 0; g < F; ++g)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int i = i0 + wi + 16 * f + mfma_row_f64(lane, v);
-                const int j = j0 + wj + 16 * g + row;
-                if (i < nr && j < nR) Psi[(size_t)i * nR + j] = make_double2(re[f][g][v], im[f][g][v]);
-            }
+            for (int q = 0; q < 4; ++q)
+                part[wave][(16 * f + mfma_row_f64(lane, q)) * T + 16 * g + row] = make_double2(re[f][g][q], im[f][g][q]);
+    __syncthreads();
+    for (int e = t; e < T * T; e += 256)
+        Psi[(size_t)(i0 + e / T) * nR + j0 + e % T] =
+            cadd(cadd(part[0][e], part[1][e]), cadd(part[2][e], part[3][e]));
 }
 
 __device__ inline double block_sum(double v, double *red) {
@@ -268,8 +259,14 @@ void launch_grid_observables(const double2 *Psi, int nr, int nR, double hr, doub
 
 void launch_observables(const Dims &d, const Bufs &b, hipStream_t s) {
     const int Np = padded(d.N);
-    const dim3 tiles((d.nR + kOT - 1) / kOT, (d.nr + kOT - 1) / kOT);
-    hipLaunchKernelGGL(k_obs_psi, tiles, dim3(256), 0, s, b.psi1, b.psi2, b.C, d.nr, d.nR, Np, b.obs_psi);
+    auto go = [&](auto kernel, int tile) {               // (the grids are powers of two >= 32)
+        hipLaunchKernelGGL(kernel, dim3(d.nR / tile, d.nr / tile), dim3(256), 0, s, b.psi1, b.psi2, b.C, d.nr, d.nR, Np,
+                           b.obs_psi);
+    };
+    // 32 x 32 tiles where there is one for a CU (whole call with tiles of 32 and
+    // 16: N = 2048 on 1024 x 256, 138 and 164 us; N = 1024 on 512 x 256, 90 and 82)
+    if ((size_t)d.nr * d.nR >= (size_t)256 * 32 * 32) go(k_obs_psi<2>, 32);
+    else go(k_obs_psi<1>, 16);
     launch_grid_observables(b.obs_psi, d.nr, d.nR, d.hr, d.hR, d.n_bo, b.bo, b.obs_chi, b.obs_part, b.obs_out, s);
     double *tail = b.obs_out + obs_len(d.nr, d.nR, d.n_bo);
     hipLaunchKernelGGL(k_obs_tail, dim3((d.N + 255) / 256), dim3(256), 0, s, b.r, b.R, b.C, b.scal, b.flags, d.N, tail);
