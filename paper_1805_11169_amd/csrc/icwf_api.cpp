@@ -109,7 +109,7 @@ Bufs carve(const icwf_config &c, char *base, size_t *total) {
     b.obs_psi = L.take<double2>(nr * nR);
     b.obs_chi = L.take<double2>(std::max<size_t>(1, nbo * nR));
     b.obs_part = L.take<double>(icwf::kRhoSlices * nR);
-    b.obs_out = L.take<double>(icwf::obs_len(c.n_r, c.n_R, c.n_bo) + icwf::obs_tail_len(c.n_traj));
+    b.obs_out = L.take<double>(icwf::obs_len(c.n_r, c.n_R, c.n_bo) + icwf::obs_tail_len((int)Np));
     b.mparams = L.take<icwf::ModelParams>(1);
     b.batch_tab = L.take<long long>(icwf::kMaxBatch);
     *total = (L.off + 255) & ~size_t(255);
