@@ -41,7 +41,7 @@ struct Dims {
 constexpr int kPad = 64;
 inline int padded(int N) { return (N + kPad - 1) / kPad * kPad; }
 constexpr int kCholNb = 64;      // Cholesky panel width
-constexpr int kLowRankMax = 64;  // most terms of a sum-of-products W_c (mixed and separable forms)
+constexpr int kLowRankMax = 64;  // most terms of a sum-of-products W_c
 constexpr int kWcReserve = 64;   // CU slots the persistent contraction leaves to the other stream
 constexpr int kWcSplitMax = 512; // most tiles the contraction splits at the end of its queue
 constexpr int kWcParts = 4;      // units per split tile (FP64 step at N = 1024: 6.32 ms with 2, 6.27 with 4)

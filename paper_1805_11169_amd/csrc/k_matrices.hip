@@ -1,13 +1,17 @@
 // The single-species matrices of Eq. 9 (9a, and the conditioned factors of
 // 9c-9d) and the two-body contraction of Eq. 9b.
 //
-// Single species (k_zgemm): out[b][a] = h sum_k conj(X[b][k]) Y[a][k] for the
+// Single species (k_zgemm, k_zgemm_split): out[b][a] = h sum_k conj(X[b][k]) Y[a][k] for the
 // pairs (X, Y) = (psi1, psi1) -> S1, (psi1, G1) -> E1, (psi2, psi2) -> S2,
 // (psi2, G2) -> E2, where G is the ket weighted by the coupling potential at
 // the ket's own trajectory: G1^a_i = W_c(r_i, R^a) psi1^a_i, G2^a_j =
 // W_c(r^a, R_j) psi2^a_j.  Complex = four real FP64 MFMA products.
 //
-// Two-body (k_wc): Wc[b][a] = hr hR sum_j conj(psi2^b_j) psi2^a_j
+// Two-body (k_wc_sep): where W_c is, to its rounding, a short sum of products
+// u_k(r) v_k(R), Wc[b][a] = hr hR sum_k (sum_i conj(psi1^b_i) psi1^a_i u_k(r_i))
+// (sum_j conj(psi2^b_j) psi2^a_j v_k(R_j)).
+//
+// Two-body without such a sum (k_wc): Wc[b][a] = hr hR sum_j conj(psi2^b_j) psi2^a_j
 //                             sum_i conj(psi1^b_i) psi1^a_i W_c(r_i, R_j)
 // for b <= a (the matrix is Hermitian).  The inner i-sum is a real GEMM whose
 // A operand, the pair product P1 = conj(psi1^b) psi1^a, is generated in

@@ -12,7 +12,7 @@
 //    for all i.  The derivative entry of the grid point nearest x^a is set to
 //    minus the sum of all others (the derivatives of the interpolant of a
 //    constant vanish), which removes the cancellation of the closed form there.
-// 2. k_vel_gemm: the four real x complex contractions
+// 2. k_vel_gemm (k_vel_split for small ensembles): the four real x complex contractions
 //        A1 = S_r psi1^T, D1 = S'_r psi1^T, A2 = S_R psi2^T, D2 = S'_R psi2^T
 //    on FP64 matrix cores (v_mfma_f64_16x16x4), 64 (a) x 32 (b) tiles staged
 //    through LDS, followed in registers by the b-sums with C over the tile.
