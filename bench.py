@@ -45,10 +45,11 @@ HBM_PEAK_GBS = 8000.0
 # any change the traffic is reported as null until measured again.
 TRAFFIC = {
     "sm_n1024": {
-        "sources_sha256_16": "f7e36e1c54569dda",
-        "fp64": 348255744.0,        # k_wc<double>: fetch 159085.2 KiB x2, write 21923.1 KiB
-        "mixed": 309099520.0,       # k_wc<float> + k_wc_sep: fetch 79068.6 + 49840.5 KiB x2, write 35651.5 + 8385.3 KiB
-        "separable": 162296422.4,   # k_wc_sep (K = 28): fetch 75053.6 KiB x2, write 8385.4 KiB
+        "sources_sha256_16": "d31924c5cb082843",
+        # k_wc_sep (K = 28) in every form: fetch 48446.9 KiB x2, write 9860.5 KiB
+        "fp64": 109316403.2,
+        "mixed": 109316403.2,
+        "separable": 109316403.2,
     },
 }
 TRAFFIC_SOURCES = ("paper_1805_11169_amd/csrc/k_matrices.hip", "paper_1805_11169_amd/csrc/icwf_device.hpp",
