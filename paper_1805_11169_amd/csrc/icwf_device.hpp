@@ -144,4 +144,13 @@ __device__ inline T *zshift(T *p, long long o) {
 enum Flag : int32_t { kFlagHalt = 0, kFlagNode = 1, kFlagSolve = 2, kFlagNonfinite = 3, kFlagOut = 4,
                       kFlagHang = 5, kNumFlags = 8 };
 
+// Whether the simulation has halted, as one thread sees it.  Another launch or
+// another work-group may raise the flag while this one runs, so the waves of a
+// work-group can see it differently: where they share more than a result
+// nobody reads after a halt (a unit of work, a ticket, data handed on), one
+// thread looks and the others take its answer through LDS.
+__device__ inline bool halted(const int32_t *flags) {
+    return __hip_atomic_load(&flags[kFlagHalt], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+}
+
 }  // namespace icwf

@@ -457,7 +457,6 @@ __global__ void __launch_bounds__(256, 2) k_wc(const typename WcTraits<T>::cplx 
     typedef WcChunk<T> CK;
     constexpr int KC = CK::KC, LDA = CK::LDA, LDW = CK::LDW, QS = KC / 4, JT = CK::JT, JF = CK::JF;
     constexpr int AROWS = CK::AROWS, WROWS = CK::WROWS;
-    if (flags[kFlagHalt]) return;
     // two staging buffers as separate arrays: the compiler can then tell the
     // reads of one from the direct loads into the other
     __shared__ __align__(16) C2 sA0[AROWS][LDA], sA1[AROWS][LDA];   // rows 0..15: a rows, 16..31: b rows
@@ -483,8 +482,12 @@ __global__ void __launch_bounds__(256, 2) k_wc(const typename WcTraits<T>::cplx 
     const int xcd = __builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)) & (kWcQueues - 1);   // HW_REG_XCC_ID
     for (;;) {
         if (threadIdx.x == 0) {
+            // a halt ends the work-group as a whole, here and nowhere else: the
+            // factorisation beside this launch may raise it at any time, and
+            // waves that each read it for themselves would part company
+            const bool go = !halted(flags);
             int got = -1, gq = 0;
-            for (int o = 0; o < kWcQueues && got < 0; ++o) {
+            for (int o = 0; go && o < kWcQueues && got < 0; ++o) {
                 const int q = (xcd + o) & (kWcQueues - 1);
                 int lo, nf, ns;
                 queue_range(q, &lo, &nf, &ns);
@@ -887,7 +890,6 @@ __global__ void __launch_bounds__(64 * kSepWaves, 2) k_wc_sep(const double2 *__r
     order = zshift(order, zo_);
     flags = zshift(flags, zo_);
 
-    if (flags[kFlagHalt]) return;
     __shared__ SepShared<B> sh;
     __shared__ int s_unit;
     const int kpad = __builtin_amdgcn_readfirstlane(*kpad_at);
@@ -896,7 +898,11 @@ __global__ void __launch_bounds__(64 * kSepWaves, 2) k_wc_sep(const double2 *__r
     const bool queued = (int)gridDim.x < units;      // else one unit per work-group
     // units from the per-XCD queues over the blocked tile order, as k_wc
     const int xcd = __builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)) & (kWcQueues - 1);   // HW_REG_XCC_ID
+    // (a halt ends the work-group as a whole, through the unit one thread
+    // takes, as in k_wc)
     auto take = [&] {
+        if (halted(flags)) return -1;
+        if (!queued) return (int)blockIdx.x;
         int got = -1;
         for (int o = 0; o < kWcQueues && got < 0; ++o) {
             const int q = (xcd + o) & (kWcQueues - 1);
@@ -908,12 +914,9 @@ __global__ void __launch_bounds__(64 * kSepWaves, 2) k_wc_sep(const double2 *__r
         }
         return got;
     };
-    int unit = blockIdx.x;
-    if (queued) {
-        if (threadIdx.x == 0) s_unit = take();
-        __syncthreads();
-        unit = s_unit;
-    }
+    if (threadIdx.x == 0) s_unit = take();
+    __syncthreads();
+    int unit = s_unit;
     for (;;) {
         unit = __builtin_amdgcn_readfirstlane(unit);
         if (unit < 0 || unit >= units) break;

@@ -620,10 +620,17 @@ __global__ void __launch_bounds__(256, 2) k_cgemm(GemmBatch g, const int32_t *__
 constexpr unsigned long long kPending = 0x7ff8dead00c0ffeeull;   // a NaN no arithmetic produces
 constexpr int kSyncTicketF = 0, kSyncTicketB = 1;
 
-__device__ inline int take_ticket(int32_t *ctr, int *slot) {
-    if (threadIdx.x == 0) *slot = atomicAdd(ctr, 1);
+// The work-group's ticket, and whether it finds the simulation halted (slot[2]
+// in LDS: every wave of it goes the same way).
+__device__ inline int take_ticket(int32_t *ctr, const int32_t *flags, int (&slot)[2], bool *halt) {
+    if (threadIdx.x == 0) {
+        const bool h = halted(flags);                // (both on their way together)
+        slot[0] = atomicAdd(ctr, 1);
+        slot[1] = h;
+    }
     __syncthreads();
-    return *slot;
+    *halt = slot[1] != 0;
+    return slot[0];
 }
 
 __device__ inline unsigned long long peek(const double *p) {
@@ -720,14 +727,14 @@ __global__ void __launch_bounds__(256) k_rk_fwd(const double2 *__restrict__ K, c
     flags = zshift(flags, zo_);
 
     __shared__ double2 yc[2][NB], uvec[NB];
-    __shared__ int slot;
-    const int B = take_ticket(&sync[kSyncTicketF], &slot);
+    __shared__ int slot[2];
+    bool halt;
+    const int B = take_ticket(&sync[kSyncTicketF], flags, slot, &halt);
     if (B == 0 && threadIdx.x == 0) sync[kSyncTicketB] = 0;
-    const bool halted = flags[kFlagHalt] != 0;
     const int t = threadIdx.x, i = t >> 2, q = t & 3;
     const int r0 = B * NB;
     if (t < NB) post_pending(&xbuf[r0 + t]);
-    if (halted) {                                    // nobody waits for ever
+    if (halt) {                                      // nobody waits for ever
         if (t < NB) post(&ybuf[r0 + t], make_double2(0, 0));
         return;
     }
@@ -840,11 +847,11 @@ __global__ void __launch_bounds__(256) k_rk_bwd(const double2 *__restrict__ L, c
     flags = zshift(flags, zo_);
 
     __shared__ double2 xc[2][NB], uvec[NB];
-    __shared__ int slot;
-    const int ticket = take_ticket(&sync[kSyncTicketB], &slot);
+    __shared__ int slot[2];
+    bool halt;
+    const int ticket = take_ticket(&sync[kSyncTicketB], flags, slot, &halt);
     const int B = nblk - 1 - ticket;
     if (ticket == 0 && threadIdx.x == 0) sync[kSyncTicketF] = 0;
-    const bool halted = flags[kFlagHalt] != 0;
     const int t = threadIdx.x, i = t >> 2, q = t & 3;
     const int r0 = B * NB;
     double2 yb = make_double2(0, 0);
@@ -852,7 +859,7 @@ __global__ void __launch_bounds__(256) k_rk_bwd(const double2 *__restrict__ L, c
         yb = ybuf[r0 + i];
         post_pending(&ybuf[r0 + i]);
     }
-    if (halted) {                                    // nobody waits for ever
+    if (halt) {                                      // nobody waits for ever
         if (q == 0) post(&xbuf[r0 + i], make_double2(0, 0));
         return;
     }
