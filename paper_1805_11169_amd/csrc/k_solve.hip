@@ -710,6 +710,13 @@ __global__ void __launch_bounds__(256) k_matvec(const double2 *__restrict__ M, c
 // threads; thread t: row i = t / 4 of the block, columns 4 c + q, q = t % 4.
 // Everything that does not depend on the blocks above (rhs_B, the block's
 // slices of L and of L_BB^-1) is loaded before the waits.
+//
+// Eq. 8 amplifies the rounding of K v by up to 1 / (2 sqrt(eps)), so its sum
+// is a shallow one: a thread adds each 16 of its terms as a tree, the trees to
+// four running sums in turn, and these and the row's four threads pairwise (at
+// Np = 1536 a chain of 6 and 8 levels above it, as a 256-lane sum has; one
+// chain of 384 terms a thread left 2.1 to 4.2 times its error at N = 400 to
+// 1984, rms against long double).
 __global__ void __launch_bounds__(256) k_rk_fwd(const double2 *__restrict__ K, const double2 *__restrict__ v,
                                                 const double2 *__restrict__ rhs, const double2 *__restrict__ L,
                                                 const double2 *__restrict__ Linv, double2 *__restrict__ ybuf,
@@ -726,7 +733,7 @@ __global__ void __launch_bounds__(256) k_rk_fwd(const double2 *__restrict__ K, c
     sync = zshift(sync, zo_);
     flags = zshift(flags, zo_);
 
-    __shared__ double2 yc[2][NB], uvec[NB];
+    __shared__ double2 yc[2][NB], uvec[NB], vc[4 * NB];
     __shared__ int slot[2];
     bool halt;
     const int B = take_ticket(&sync[kSyncTicketF], flags, slot, &halt);
@@ -738,16 +745,45 @@ __global__ void __launch_bounds__(256) k_rk_fwd(const double2 *__restrict__ K, c
         if (t < NB) post(&ybuf[r0 + t], make_double2(0, 0));
         return;
     }
+    // row i of K v, 128 columns of K in flight at a time and v through LDS
+    double2 kv[4] = {};
+    if (K) {
+        const double2 *krow = K + (size_t)(r0 + i) * Np + q;
+        for (int g = 0; g < Np; g += 4 * NB) {
+            if (g > 0) __syncthreads();              // the previous columns' v is read
+            vc[t] = g + t < Np ? v[g + t] : make_double2(0, 0);
+            double2 x[2][16];
+#pragma unroll
+            for (int h = 0; h < 4; h += 2) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    if (g + (h + u) * NB < Np)
+#pragma unroll
+                        for (int c = 0; c < 16; ++c) x[u][c] = krow[g + (h + u) * NB + 4 * c];
+                if (h == 0) __syncthreads();
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    if (g + (h + u) * NB >= Np) break;
+#pragma unroll
+                    for (int c = 0; c < 16; ++c) x[u][c] = cmul(x[u][c], vc[(h + u) * NB + 4 * c + q]);
+#pragma unroll
+                    for (int w = 8; w > 0; w >>= 1)
+#pragma unroll
+                        for (int c = 0; c < w; ++c) x[u][c] = cadd(x[u][c], x[u][c + w]);
+                    kv[h + u] = cadd(kv[h + u], x[u][0]);
+                }
+            }
+        }
+        kv[0] = cadd(cadd(kv[0], kv[1]), cadd(kv[2], kv[3]));
+        kv[0].x += __shfl_xor(kv[0].x, 1);
+        kv[0].y += __shfl_xor(kv[0].y, 1);
+        kv[0].x += __shfl_xor(kv[0].x, 2);
+        kv[0].y += __shfl_xor(kv[0].y, 2);
+    }
     double2 iv[16];   // row i of L_BB^-1
 #pragma unroll
     for (int c = 0; c < 16; ++c) iv[c] = Linv[(size_t)(r0 + i) * NB + 4 * c + q];
     double2 part = make_double2(0, 0);
-    if (K) {
-        // minus row i of K v
-        const double2 *krow = K + (size_t)(r0 + i) * Np + q;
-#pragma unroll 8
-        for (int c = 0; c < Np / 4; ++c) part = csub(part, cmul(krow[4 * c], v[4 * c + q]));
-    }
     // contributions of the blocks above, as they complete: the words of block
     // C are awaited by the first 128 threads
     const double *words = reinterpret_cast<const double *>(ybuf);
@@ -770,7 +806,7 @@ __global__ void __launch_bounds__(256) k_rk_fwd(const double2 *__restrict__ K, c
     part.y += __shfl_xor(part.y, 1);
     part.x += __shfl_xor(part.x, 2);
     part.y += __shfl_xor(part.y, 2);
-    if (q == 0) uvec[i] = K ? make_double2(-part.x, -part.y) : csub(rhs[r0 + i], part);
+    if (q == 0) uvec[i] = csub(K ? kv[0] : rhs[r0 + i], part);
     __syncthreads();
     double2 y = make_double2(0, 0);
 #pragma unroll
