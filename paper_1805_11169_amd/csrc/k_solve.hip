@@ -154,7 +154,11 @@ __device__ inline double bcast(double v, int src) {
 // the 16 x 16 triangle meanwhile.  The rows below are solved transposed,
 // L11 Z = A21^H, 16 rows per wave: the accumulator layout of a matrix product
 // is the layout of its right operand, so Z_J = L_JJ^-1 (A_J^H - sum_I L_JI Z_I)
-// runs from register to register.  What bounds it is the chain of 64 columns
+// runs from register to register.  Products are summed by themselves and then
+// subtracted: accumulated onto the entry, each product rounded it twice (re
+// and im of the factors), and the solves' error was a quarter larger (N = 250,
+// mean of 8 ensembles against long double, relative to LAPACK's: 1.76, 1.37
+// so).  What bounds it is the chain of 64 columns
 // (a panel 30-36 us alone, 65-71 us on a compute unit that also runs the
 // contraction, whose matrix products hold the FP64 pipe 64 cycles at a time):
 // two matrices at N = 64, all kernels of the factorisation, 105 -> 37 us
@@ -172,12 +176,12 @@ struct PanelShared {
     double dinv[NB];
 };
 
-// acc += s X Y^H for 16 x 16 tiles in LDS, s = +-1
-__device__ __forceinline__ void tile_mul_h(dbl4 &re, dbl4 &im, const Tile &X, const Tile &Y, double s) {
+// acc += X Y^H for 16 x 16 tiles in LDS
+__device__ __forceinline__ void tile_mul_h(dbl4 &re, dbl4 &im, const Tile &X, const Tile &Y) {
     const int lane = threadIdx.x & 63, row = lane & 15, quarter = lane >> 4;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const double2 x = cscale(X[row][4 * q + quarter], s), y = Y[row][4 * q + quarter];
+        const double2 x = X[row][4 * q + quarter], y = Y[row][4 * q + quarter];
         re = mfma(x.x, y.x, re);
         re = mfma(x.y, y.y, re);
         im = mfma(x.y, y.x, im);
@@ -345,10 +349,10 @@ __global__ void __launch_bounds__(256, 2) k_chol_panel(double2 *A0, double2 *A1,
         for (int K = J + 1; K < 4; ++K)
             for (int I = K; I < 4; ++I, ++n) {
                 if ((n & 3) != wave) continue;
-                dbl4 re, im;
+                dbl4 re, im, pre = {0, 0, 0, 0}, pim = {0, 0, 0, 0};
                 tile_load(re, im, sh.L[tile_of(I, K)]);
-                tile_mul_h(re, im, sh.L[tile_of(I, J)], sh.L[tile_of(K, J)], -1.0);
-                tile_store(sh.L[tile_of(I, K)], re, im);
+                tile_mul_h(pre, pim, sh.L[tile_of(I, J)], sh.L[tile_of(K, J)]);
+                tile_store(sh.L[tile_of(I, K)], re - pre, im - pim);
             }
         __syncthreads();
     }
@@ -362,10 +366,10 @@ __global__ void __launch_bounds__(256, 2) k_chol_panel(double2 *A0, double2 *A1,
     if (!own) {
 #pragma unroll
         for (int J = 0; J < 4; ++J) {
+            dbl4 re = {0, 0, 0, 0}, im = {0, 0, 0, 0}, sre = {0, 0, 0, 0}, sim = {0, 0, 0, 0};
 #pragma unroll
-            for (int I = 0; I < J; ++I) tile_mul(zre[J], zim[J], sh.L[tile_of(J, I)], zre[I], zim[I], -1.0);
-            dbl4 re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
-            tile_mul(re, im, sh.inv[J], zre[J], zim[J], 1.0);
+            for (int I = 0; I < J; ++I) tile_mul(sre, sim, sh.L[tile_of(J, I)], zre[I], zim[I], 1.0);
+            tile_mul(re, im, sh.inv[J], zre[J] - sre, zim[J] - sim, 1.0);
             zre[J] = re;
             zim[J] = im;
 #pragma unroll
