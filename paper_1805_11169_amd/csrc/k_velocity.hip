@@ -274,52 +274,66 @@ __global__ void __launch_bounds__(256) k_vel_gemm(const double *__restrict__ Sr,
 }
 
 // The same where 64 x 32 tiles are too few for the device: 16 (a) x 32 (b)
-// per work-group, its eight waves taking the 8-point steps of both grids in
-// turn, operands straight from global memory one step ahead.  The partial
-// sums meet in LDS, a fragment of columns and a species at a time; wave v < 4
-// keeps accumulator register v of all eight of them and forms the three
-// products with C_b.
+// per work-group, its eight waves taking an eighth of both grids each, in
+// steps of 8 points, operands straight from global memory one step ahead.  The
+// partial sums meet in LDS, a fragment of columns and a species at a time;
+// wave v < 4 keeps accumulator register v of all eight of them and forms the
+// three products with C_b.
+// The points keep their order (a matrix product four neighbours, a wave one
+// stretch of the grid): the terms of S' alternate in sign and neighbours
+// cancel before they round.  With the two points that a lane loads taken one
+// product apart (every second point first) and steps dealt out to the waves in
+// turn, the velocities had 1.5 to 3.1 times the error of k_vel_gemm's; so, 0.7
+// to 1.1 times.  The tables are loaded two points a lane all the same and put
+// in order between the rows of 16 lanes (8-byte loads: 3.6 % of the step at N =
+// 64).
 constexpr int kVelWaves = 8;
+
+// Rows of 16 lanes holding the pairs of points (0, 1), (4, 5), (2, 3), (6, 7)
+// to the points 0, 1, 2, 3 and 4, 5, 6, 7.
+__device__ __forceinline__ void in_order(dbl2 &x) {
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(x.x), __double2loint(x.y), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x.x), __double2hiint(x.y), false, false);
+    x.x = __hiloint2double(hi[0], lo[0]);
+    x.y = __hiloint2double(hi[1], lo[1]);
+}
 
 __device__ __forceinline__ void vel_steps(const double *Sg, const double *Dg, const double2 *Pg, int K, int a0, int b0,
                                           int wave, dbl4 (&acc)[2][4]) {
-    constexpr int EP = 2;                            // consecutive points per lane
+    constexpr int EP = 2;                            // matrix products (4 points) of a step
     const int lane = threadIdx.x & 63, row = lane & 15, quarter = lane >> 4;
 #pragma unroll
     for (int g = 0; g < 2; ++g)
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[g][i] = dbl4{0, 0, 0, 0};
-    const int count = (K / (4 * EP) - wave + kVelWaves - 1) / kVelWaves;
-    if (count <= 0) return;
-    const gchar *sat = opaque(Sg + (size_t)a0 * K + 4 * EP * wave), *dat = opaque(Dg + (size_t)a0 * K + 4 * EP * wave);
-    const gchar *pat = opaque(Pg + (size_t)b0 * K + 4 * EP * wave);
-    const uint32_t toff = (uint32_t)row * K * 8u + quarter * 8u * EP, poff = 2 * toff, frow = 256u * K;
-    dbl2 s[EP / 2], d[EP / 2], p[2][EP];
+    const int steps = K / (4 * EP), count = steps < kVelWaves ? 1 : steps / kVelWaves;   // (K is a power of two)
+    if (wave * count >= steps) return;
+    const size_t at = (size_t)wave * count * 4 * EP;
+    const gchar *sat = opaque(Sg + (size_t)a0 * K + at), *dat = opaque(Dg + (size_t)a0 * K + at);
+    const gchar *pat = opaque(Pg + (size_t)b0 * K + at);
+    const int pair = 2 * (quarter & 1) + (quarter >> 1);
+    const uint32_t toff = (uint32_t)row * K * 8u + pair * 16u, poff = (uint32_t)row * K * 16u + quarter * 16u;
+    const uint32_t frow = 256u * K;
+    dbl2 s, d, p[2][EP];
     auto load = [&]() __attribute__((always_inline)) {
-#pragma unroll
-        for (int e = 0; e < EP / 2; ++e) {
-            s[e] = *reinterpret_cast<const gdouble2 *>(sat + toff + 16u * e);
-            d[e] = *reinterpret_cast<const gdouble2 *>(dat + toff + 16u * e);
-        }
+        s = *reinterpret_cast<const gdouble2 *>(sat + toff);
+        d = *reinterpret_cast<const gdouble2 *>(dat + toff);
 #pragma unroll
         for (int g = 0; g < 2; ++g)
 #pragma unroll
-            for (int e = 0; e < EP; ++e) p[g][e] = *reinterpret_cast<const gdouble2 *>(pat + (size_t)g * frow + poff + 16u * e);
+            for (int e = 0; e < EP; ++e) p[g][e] = *reinterpret_cast<const gdouble2 *>(pat + (size_t)g * frow + poff + 64u * e);
         pin_loads();
     };
     load();
     for (int n = 0; n < count; ++n) {
-        dbl2 sc[EP / 2], dc[EP / 2], pc[2][EP];
-#pragma unroll
-        for (int e = 0; e < EP / 2; ++e) {
-            sc[e] = s[e];
-            dc[e] = d[e];
-        }
+        dbl2 sc = s, dc = d, pc[2][EP];
+        in_order(sc);
+        in_order(dc);
 #pragma unroll
         for (int g = 0; g < 2; ++g)
 #pragma unroll
             for (int e = 0; e < EP; ++e) pc[g][e] = p[g][e];
-        const size_t st = n + 1 < count ? 32u * EP * kVelWaves : 0;   // the last step loads its own operands again (never used)
+        const size_t st = n + 1 < count ? 32u * EP : 0;   // the last step loads its own operands again (never used)
         sat += st;
         dat += st;
         pat += 2 * st;
@@ -328,11 +342,10 @@ __device__ __forceinline__ void vel_steps(const double *Sg, const double *Dg, co
         for (int e = 0; e < EP; ++e)
 #pragma unroll
             for (int g = 0; g < 2; ++g) {
-                const double sv = sc[e / 2][e & 1], dv = dc[e / 2][e & 1];
-                acc[g][0] = mfma_f64(sv, pc[g][e].x, acc[g][0]);
-                acc[g][1] = mfma_f64(sv, pc[g][e].y, acc[g][1]);
-                acc[g][2] = mfma_f64(dv, pc[g][e].x, acc[g][2]);
-                acc[g][3] = mfma_f64(dv, pc[g][e].y, acc[g][3]);
+                acc[g][0] = mfma_f64(sc[e], pc[g][e].x, acc[g][0]);
+                acc[g][1] = mfma_f64(sc[e], pc[g][e].y, acc[g][1]);
+                acc[g][2] = mfma_f64(dc[e], pc[g][e].x, acc[g][2]);
+                acc[g][3] = mfma_f64(dc[e], pc[g][e].y, acc[g][3]);
             }
     }
 }
