@@ -33,7 +33,7 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-PEAK = {"fp64": 78.6, "mixed": 157.3, "separable": 78.6}   # dense matrix-core TFLOP/s of MI355X (FP64, FP32)
+PEAK = {"fp64": 78.6, "mixed": 157.3}   # dense matrix-core TFLOP/s of MI355X (FP64, FP32)
 HBM_PEAK_GBS = 8000.0
 
 # HBM traffic of one two-body contraction launch on the N = 1024, 512 x 256
@@ -294,7 +294,7 @@ def main():
         kt[name] = (n, ms)
     sim.set_timing(False)
     obs = sim.observables()
-    rank = sim.contraction_rank()
+    rank, route = sim.contraction_rank(), sim.contraction_route()
     # observables on demand (norm, both densities): launches, copy-out and sync
     torch.cuda.synchronize()
     t_obs = time.perf_counter()
@@ -305,16 +305,14 @@ def main():
     del stream
 
     wc_flops, single_flops, prop_bytes = algorithmic_counts(N, nr, nR)
-    # the contraction through K products (all of it in every form where W_c is such a sum to its rounding; the mixed
-    # form's FP32 pass else has whole blocks of 16 beside it): N(N+1)/2 pairs x (n_r + n_R) x K complex x real
-    # multiply-adds, in FP64
-    products = rank > 0 and (args.precision != "mixed" or rank % 16 != 0)
-    peak = PEAK["fp64"] if products else PEAK[args.precision]
-    if products:
+    # the contraction through K products: N(N+1)/2 pairs x (n_r + n_R) x K complex x real multiply-adds, in FP64
+    fp32 = route == icwf.CONTRACTION_FP32
+    peak = PEAK["mixed" if fp32 else "fp64"]
+    if route == icwf.CONTRACTION_PRODUCTS:
         wc_flops = 2.0 * N * (N + 1) * (nr + nR) * rank
     # the cavity's bilinear coupling leaves no contraction: the Hermitian single-species products S1, S2, <r>, <R> are
     # the dominant kernel, and the whole of the S/H build
-    bilinear = products and wl.model == inputs.MODEL_CAVITY
+    bilinear = route == icwf.CONTRACTION_BILINEAR
     dominant = "zgemm" if bilinear else "wc_contract"
     if bilinear:
         wc_flops = 8.0 * N * (N + 1) * (nr + nR)
@@ -329,7 +327,7 @@ def main():
     # n_r n_R >= 256 Np.  The build then spans the
     # longer of the two; otherwise they run one after the other.
     Np = (N + 63) // 64 * 64
-    dense = not products
+    dense = route in (icwf.CONTRACTION_TABLE, icwf.CONTRACTION_FP32)
     sinv = Np >= 1024 and (Np & (Np - 1)) == 0
     roomy = dense and nr * nR >= 256 * Np
     concurrent = Np >= 1024 and dense and ((args.precision == "fp64" and not sinv) or roomy)
@@ -353,7 +351,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32-contraction/f64" if prec == icwf.PREC_MIXED else "f64",
+        "dtype": "f32-contraction/f64" if fp32 else "f64",
         "data": "synthetic",
         "config": {"workload": wl.name, "hamiltonian": {1: "shin_metiu", 2: "cavity"}[wl.model], "n_traj": N,
                    "n_r": nr, "n_R": nR,

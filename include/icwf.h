@@ -246,6 +246,16 @@ icwf_status icwf_kernel_time(icwf_sim *sim, const char *name, int64_t *launches,
  * summed.  *rank: caller-owned host int32.  ICWF_EINVAL on NULL. */
 icwf_status icwf_contraction_rank(const icwf_sim *sim, int32_t *rank);
 
+/* How the handle forms Eq. 9b (the choice is made at creation): an
+ * icwf_contraction.  *route: caller-owned host int32.  ICWF_EINVAL on NULL. */
+typedef enum {
+    ICWF_CONTRACTION_TABLE = 0,    /* the W_c table, in FP64                                   */
+    ICWF_CONTRACTION_PRODUCTS = 1, /* the sum of products alone, in FP64                       */
+    ICWF_CONTRACTION_BILINEAR = 2, /* W_c = lam r R: from the matrices of r and R, in FP64     */
+    ICWF_CONTRACTION_FP32 = 3      /* the table less a rank-K part in FP32, that part in FP64  */
+} icwf_contraction;
+icwf_status icwf_contraction_route(const icwf_sim *sim, int32_t *route);
+
 /* Release the handle (not the workspace).  NULL is ignored. */
 void icwf_destroy(icwf_sim *sim);
 

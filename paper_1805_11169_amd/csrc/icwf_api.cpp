@@ -933,6 +933,12 @@ icwf_status icwf_contraction_rank(const icwf_sim *s, int32_t *rank) {
     return ICWF_OK;
 }
 
+icwf_status icwf_contraction_route(const icwf_sim *s, int32_t *route) {
+    if (!s || !route) return ICWF_EINVAL;
+    *route = icwf::contraction_route(s->d);
+    return ICWF_OK;
+}
+
 icwf_status icwf_kernel_time(icwf_sim *s, const char *name, int64_t *launches, double *total_ms) {
     if (!s || !name) return fail(s, ICWF_EINVAL, "NULL argument");
     HIP_OK(hipStreamSynchronize(s->stream), s);

@@ -191,7 +191,9 @@ void launch_single_species(const Dims &d, const Bufs &b, bool both_conditionings
 // E1b, E2b alone.
 void launch_single_species_next(const Dims &d, const Bufs &b, hipStream_t s);
 
-// Two-body contraction Wc (upper pair tiles), FP64 or FP32 matrix cores.
+// Two-body contraction Wc (upper pair tiles), FP64 or FP32 matrix cores, by
+// the route contraction_route names (an icwf_contraction).
+int contraction_route(const Dims &d);
 void launch_wc(const Dims &d, const Bufs &b, hipStream_t s);
 
 // The step's matrices from the single-species and two-body blocks:

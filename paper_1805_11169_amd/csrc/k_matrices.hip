@@ -1048,8 +1048,18 @@ static void launch_wc_sep(const Dims &d, const Bufs &b, int accumulate, hipStrea
     else go(d.zoff ? k_wc_sep<4, true> : k_wc_sep<4, false>, 4);
 }
 
+int contraction_route(const Dims &d) {
+    if (d.bilinear) return ICWF_CONTRACTION_BILINEAR;
+    if (d.products) return ICWF_CONTRACTION_PRODUCTS;
+    // the FP32 pass tiles the grid in chunks of 64 x 64 points: smaller grids
+    // take the dense FP64 contraction of the whole table instead
+    const bool fp32_fits = d.nr >= WcChunk<float>::KC && d.nR >= WcChunk<float>::JT;
+    return d.prec == 1 && fp32_fits ? ICWF_CONTRACTION_FP32 : ICWF_CONTRACTION_TABLE;
+}
+
 void launch_wc(const Dims &d, const Bufs &b, hipStream_t s) {
-    if (d.bilinear) return;                          // the assembly multiplies <b|r|a> by <b|R|a>
+    const int route = contraction_route(d);
+    if (route == ICWF_CONTRACTION_BILINEAR) return;  // the assembly multiplies <b|r|a> by <b|R|a>
     const int Np = padded(d.N);
     const int T16 = Np / 16;
     const int blocks = T16 * (T16 + 1) / 2;
@@ -1063,12 +1073,9 @@ void launch_wc(const Dims &d, const Bufs &b, hipStream_t s) {
         *spq = wc_split_per_queue(nsplit);   // split tiles per queue
     };
     int nparts, spq;
-    // the FP32 pass tiles the grid in chunks of 64 x 64 points: smaller grids
-    // take the dense FP64 contraction of the whole table instead
-    const bool fp32_fits = d.nr >= WcChunk<float>::KC && d.nR >= WcChunk<float>::JT;
-    if (d.products) {
+    if (route == ICWF_CONTRACTION_PRODUCTS) {
         launch_wc_sep(d, b, 0, s);
-    } else if (d.prec == 1 && fp32_fits) {
+    } else if (route == ICWF_CONTRACTION_FP32) {
         // mixed: FP32 matrix cores on the residual of the rank-K split, FP64 rank-K part added
         split(WcChunk<float>::JT, &nparts, &spq);
         launch_fill_i32(b.wc_queue, kWcQueues + kWcQueues * spq, 0, s, d.batch, d.zoff);

@@ -22,11 +22,12 @@ PREC_FP64, PREC_MIXED, PREC_SEPARABLE = 0, 1, 2
 SOLVER_AUTO, SOLVER_TRIANGULAR, SOLVER_INVERSE = 0, 1, 2
 PROP_SPLIT, PROP_CRANK_NICOLSON = 0, 1
 TRAJ_EULER, TRAJ_HEUN = 0, 1
+CONTRACTION_TABLE, CONTRACTION_PRODUCTS, CONTRACTION_BILINEAR, CONTRACTION_FP32 = 0, 1, 2, 3
 
 # the entry points include/icwf.h declares
 EXPORTS = ("icwf_workspace_bytes", "icwf_create", "icwf_step", "icwf_step_batch", "icwf_sync", "icwf_observables",
            "icwf_get_state", "icwf_get_matrices", "icwf_velocities", "icwf_set_timing", "icwf_kernel_time",
-           "icwf_contraction_rank",
+           "icwf_contraction_rank", "icwf_contraction_route",
            "icwf_destroy", "icwf_last_error", "icwf_status_string")
 # the entry points include/icwf_serve.h declares
 SERVE_EXPORTS = ("icwf_server_create", "icwf_server_submit", "icwf_server_wait", "icwf_server_result",
@@ -124,6 +125,8 @@ def lib():
         L.icwf_kernel_time.restype = c_int32
         L.icwf_contraction_rank.argtypes = [c_void_p, POINTER(c_int32)]
         L.icwf_contraction_rank.restype = c_int32
+        L.icwf_contraction_route.argtypes = [c_void_p, POINTER(c_int32)]
+        L.icwf_contraction_route.restype = c_int32
         L.icwf_destroy.argtypes = [c_void_p]
         L.icwf_destroy.restype = None
         L.icwf_last_error.argtypes = [c_void_p]
@@ -411,6 +414,11 @@ class Simulation:
     def contraction_rank(self):
         k = c_int32()
         self._check(lib().icwf_contraction_rank(self.h, byref(k)))
+        return k.value
+
+    def contraction_route(self):
+        k = c_int32()
+        self._check(lib().icwf_contraction_route(self.h, byref(k)))
         return k.value
 
     def close(self):
