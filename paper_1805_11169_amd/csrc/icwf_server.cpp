@@ -20,6 +20,7 @@
 #include "../../include/icwf_serve.h"
 #include "arena.hpp"
 #include "icwf_internal.hpp"
+#include "step_cost.hpp"
 
 namespace {
 
@@ -30,7 +31,7 @@ struct Request {
     icwf_config cfg{};
     int32_t n_steps = 0;
     size_t ws = 0;
-    double cost = 1.0;             // estimated device time of one step (ms), for equal-time turns
+    double cost = 1.0;             // estimated device time of one step (ms), set on admission
     std::vector<double> r0, R0, psi1, psi2, C0, b0, bo;
     bool has_C0 = false;
     // result
@@ -87,21 +88,6 @@ struct icwf_server {
 };
 
 namespace {
-
-// Estimated device time of one step (ms): a launch-bound floor plus the
-// step's flops at a sustained 40 TFLOP/s (the two-body contraction, dense or,
-// where that is less, through some 32 rank factors, the single-species
-// products and velocities, two complex factorisations).  Only ratios between simulations matter: the
-// scheduler gives every simulation turns of about the same device time.
-double step_cost_ms(const icwf_config &c) {
-    const double N = (double)((c.n_traj + 63) / 64 * 64), nr = c.n_r, nR = c.n_R;
-    const double pairs = 0.5 * N * (N + 1.0);
-    double contraction = 4.0 * pairs * nr * nR;
-    const double products = 4.0 * pairs * (nr + nR) * 32.0;
-    if (c.precision == ICWF_PREC_SEPARABLE || products < contraction) contraction = products;
-    const double rest = 28.0 * N * N * (nr + nR) + 2.0 * (8.0 / 3.0) * N * N * N;
-    return 0.4 + (contraction + rest) / 4e10;
-}
 
 void set_message(Request &rq, const std::string &m) {
     std::strncpy(rq.info.message, m.c_str(), sizeof(rq.info.message) - 1);
@@ -198,6 +184,10 @@ void admit(icwf_server *S, int idx, const std::shared_ptr<Request> &rq, size_t o
         complete(S, rq, true, off);
         return;
     }
+    int32_t route = 0, rank = 0;
+    (void)icwf_contraction_route(sim, &route);
+    (void)icwf_contraction_rank(sim, &rank);
+    rq->cost = icwf::step_cost_ms(rq->cfg, route, rank);
     sl.sim = sim;
     sl.req = rq;
     sl.off = off;
@@ -255,14 +245,10 @@ bool poll(icwf_server *S, Slot &sl, bool *gone) {
     return progress;
 }
 
-// Steps of the slot's next turn: steps_per_turn for the costliest resident
-// simulation, proportionally more for cheaper ones (turns of about equal
-// device time, so that a small simulation is not held to the pace of the
-// largest), never past its last step.
+// Steps of the slot's next turn (turns of about equal device time, so that a
+// small simulation is not held to the pace of the largest).
 int32_t turn_steps(const icwf_server *S, const Slot &sl, double ref_cost) {
-    const double scale = std::max(1.0, ref_cost / sl.req->cost);
-    const double k = std::min(S->cfg.steps_per_turn * scale, 1e6);
-    return std::max(1, std::min((int32_t)k, sl.req->n_steps - sl.enqueued));
+    return icwf::turn_steps(S->cfg.steps_per_turn, ref_cost, sl.req->cost, sl.req->n_steps - sl.enqueued);
 }
 
 double reference_cost(const icwf_server *S) {
@@ -434,7 +420,6 @@ icwf_status icwf_server_submit(icwf_server *S, const icwf_config *cfg, const dou
     rq->cfg = *cfg;
     rq->n_steps = n_steps;
     rq->ws = ws;
-    rq->cost = step_cost_ms(*cfg);
     rq->r0.assign(r0, r0 + N);
     rq->R0.assign(R0, R0 + N);
     rq->psi1.assign(psi1_0, psi1_0 + 2 * N * nr);
