@@ -309,7 +309,7 @@ void timed(icwf_sim *s, const char *name, hipStream_t st, F fn) {
 constexpr int kOverlapMinN = 1024;
 
 void enqueue_step(icwf_sim *s, const Dims &d, int parity, hipStream_t st, hipStream_t side) {
-    if (s->Np < kOverlapMinN || d.bilinear) side = st;   // (bilinear: nothing to run beside the factorisations)
+    if (s->Np < kOverlapMinN || d.bilinear) side = st;   // (bilinear: no contraction to run beside the factorisations)
     const Bufs &b = s->b;
     const bool heun = d.traj == ICWF_TRAJ_HEUN;
     timed(s, "velocity", st, [&] { icwf::launch_velocity(d, b, icwf::kVelocityEuler, st); });
@@ -629,14 +629,15 @@ icwf_status icwf_create(const icwf_config *cfg, const double *r0, const double *
     d.bilinear = cfg->model == ICWF_MODEL_CAVITY && d.products;
     if (d.fp32_residual)
         for (size_t e = 0; e < res.size(); ++e) wc32[e] = static_cast<float>(res[e]);
-    // a contraction through few products is the short branch of a forked
-    // step where (n_r + n_R) K < 32 N (K in blocks of 16): it then takes five
-    // work-groups per four CUs and leaves room to the factorisation stream
-    // (N = 1024 on 512 x 256, K = 28: 2.22 ms per step, 2.23 with one per CU,
-    // 2.38 with the 2 ncu - 64 of the longer contractions; N = 2048 cavity, K =
-    // 1: 8.46, 8.96 and 8.86; but N = 1500 on 1024 x 512, K = 29, on the other
-    // side of the line: 7.75, 8.29 and 7.23)
-    if (d.products && Np >= kOverlapMinN && (size_t)(nr + nR) * 16 * blocks(d.lr_rank) < 32 * (size_t)Np)
+    // a contraction through few products takes five work-groups per four CUs
+    // of a forked step and leaves room to the factorisation stream; through
+    // more, 2 ncu - 64 as the dense one.  The line is in (n_r + n_R) K (K in
+    // blocks of 16), whatever N (ms per step, 5/4 and 2 ncu - 64): 12288, N =
+    // 1500 3.34 and 3.80, 3000 10.9 and 12.5; 24576, N = 1024 2.28 and 2.38,
+    // 2048 7.76 and 7.95, 4096 32.0 and 33.4; but 40960, N = 1088 3.60 and
+    // 3.38, 2048 11.1 and 10.4; 49152, N = 1024 3.37 and 3.29, 1600 7.97 and
+    // 7.12, 2048 12.7 and 11.6; 81920, N = 1024 5.24 and 4.88
+    if (d.products && Np >= kOverlapMinN && (size_t)(nr + nR) * 16 * blocks(d.lr_rank) <= 32768)
         d.wc_grid = ncu + ncu / 4;
     // rank factors in blocks of 16, laid out [block][n / 2][16][2] as the contraction's lanes read them
     auto rank_blocks = [&](const std::vector<double> &f, int n) {
