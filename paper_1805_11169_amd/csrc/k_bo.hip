@@ -258,10 +258,6 @@ __device__ void spectral_wave(const BoArgs &A, const double *u, const double *v,
     wave_sync();
 }
 
-// Waves with a transform buffer: all, but for 1024 points, where eight buffers
-// are more LDS than there is.
-constexpr int fft_waves(int log2n) { return log2n < 10 ? kBoWaves : 4; }
-
 // h_e or the preconditioner on `cols` columns of `in`, to `out`.
 template <int LOG2N>
 __device__ void apply_columns(const BoArgs &A, const double *in, double *out, int cols, const double *V,
@@ -269,7 +265,7 @@ __device__ void apply_columns(const BoArgs &A, const double *in, double *out, in
     constexpr int n = 1 << LOG2N;
     if constexpr (LOG2N <= 10) {
         const int wave = threadIdx.x >> 6;
-        for (int q = wave < fft_waves(LOG2N) ? 2 * wave : cols; q < cols; q += 2 * fft_waves(LOG2N)) {
+        for (int q = 2 * wave; q < cols; q += 2 * kBoWaves) {
             const bool two = q + 1 < cols;
             const double *u = in + (size_t)q * n;
             double *ou = out + (size_t)q * n;
@@ -310,8 +306,9 @@ __device__ void gram(const double *X, const double *Y, int k, double *G, double 
 #pragma unroll
             for (int v = 0; v < 4; ++v) part[wave][16 * mfma_row_f64(lane, v) + row] = acc[v];
             __syncthreads();
+            static_assert(kBoThreads == 256, "a thread for each entry of the tile");
             const int a = a0 + (tid >> 4), b = b0 + (tid & 15);
-            if (tid < 256 && a < k && b < k && a <= b) {
+            if (a < k && b < k && a <= b) {
                 double g = part[0][tid];
 #pragma unroll
                 for (int w = 1; w < kBoWaves; ++w) g += part[w][tid];
@@ -551,7 +548,7 @@ __device__ inline double unit_hash(unsigned long long x) {
 template <int LOG2N, int MZ>
 __global__ void __launch_bounds__(kBoThreads, MZ <= 15 ? 2 : 1) k_bo_lobpcg(BoArgs A) {
     constexpr int n = 1 << LOG2N;
-    constexpr int kTransform = LOG2N <= 10 ? fft_waves(LOG2N) * (n + n / 8) : n;
+    constexpr int kTransform = LOG2N <= 10 ? kBoWaves * (n + n / 8) : n;
     constexpr int kTwiddles = LOG2N <= 10 ? n / 2 : 1;
     __shared__ double2 fb[kTransform];
     __shared__ double2 tw[kTwiddles];
