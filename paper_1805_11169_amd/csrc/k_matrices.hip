@@ -485,9 +485,10 @@ __global__ void __launch_bounds__(256, 2) k_wc(const typename WcTraits<T>::cplx 
             // a halt ends the work-group as a whole, here and nowhere else: the
             // factorisation beside this launch may raise it at any time, and
             // waves that each read it for themselves would part company
-            const bool go = !halted(flags);
+            // (read with the queue, not ahead of it)
+            const bool halt = halted(flags);
             int got = -1, gq = 0;
-            for (int o = 0; go && o < kWcQueues && got < 0; ++o) {
+            for (int o = 0; o < kWcQueues && got < 0; ++o) {
                 const int q = (xcd + o) & (kWcQueues - 1);
                 int lo, nf, ns;
                 queue_range(q, &lo, &nf, &ns);
@@ -499,7 +500,7 @@ __global__ void __launch_bounds__(256, 2) k_wc(const typename WcTraits<T>::cplx 
                     gq = q;
                 }
             }
-            s_unit = got;
+            s_unit = halt ? -1 : got;
             s_queue = gq;
         }
         __syncthreads();
@@ -901,9 +902,8 @@ __global__ void __launch_bounds__(64 * kSepWaves, 2) k_wc_sep(const double2 *__r
     // (a halt ends the work-group as a whole, through the unit one thread
     // takes, as in k_wc)
     auto take = [&] {
-        if (halted(flags)) return -1;
-        if (!queued) return (int)blockIdx.x;
-        int got = -1;
+        const bool halt = halted(flags);
+        int got = queued ? -1 : (int)blockIdx.x;
         for (int o = 0; o < kWcQueues && got < 0; ++o) {
             const int q = (xcd + o) & (kWcQueues - 1);
             const int lo = (int)((long long)q * units / kWcQueues);
@@ -912,7 +912,7 @@ __global__ void __launch_bounds__(64 * kSepWaves, 2) k_wc_sep(const double2 *__r
             const int k = atomicAdd(&queue[q], 1);
             if (k < n) got = lo + k;
         }
-        return got;
+        return halt ? -1 : got;
     };
     if (threadIdx.x == 0) s_unit = take();
     __syncthreads();
