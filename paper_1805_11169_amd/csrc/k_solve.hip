@@ -617,8 +617,8 @@ __global__ void __launch_bounds__(256, 2) k_cgemm(GemmBatch g, const int32_t *__
 // itself: every entry holds kPending until its block writes it, and whoever
 // needs it reads it until it holds something else, so a hand-off is one store
 // and one load (with a flag beside the data: a store, a fence, a flag, and a
-// load of each; the step's four stages, N = 250: 172 -> 108 us, N = 500: 326 ->
-// 195 us, N = 1500: 1.09 -> 0.66 ms, K v taken into the forward kernel).  k_rk_bwd puts kPending back into the y it has read,
+// load of each; the step's four stages, N = 250: 172 -> 99 us, N = 500: 326 ->
+// 183 us, N = 1500: 1.09 -> 0.60 ms, K v taken into the forward kernel).  k_rk_bwd puts kPending back into the y it has read,
 // k_rk_fwd into the x of the stage before; the words start so at create.
 // solve_sync: the two tickets, each kernel clearing the other's.
 constexpr unsigned long long kPending = 0x7ff8dead00c0ffeeull;   // a NaN no arithmetic produces
