@@ -45,11 +45,11 @@ HBM_PEAK_GBS = 8000.0
 # any change the traffic is reported as null until measured again.
 TRAFFIC = {
     "sm_n1024": {
-        "sources_sha256_16": "d31924c5cb082843",
-        # k_wc_sep (K = 28) in every form: fetch 48446.9 KiB x2, write 9860.5 KiB
-        "fp64": 109316403.2,
-        "mixed": 109316403.2,
-        "separable": 109316403.2,
+        "sources_sha256_16": "04e62df8cbd2c6c2",
+        # k_wc_sep (K = 28) in every form: fetch 48126.6 KiB x2, write 9860.7 KiB
+        "fp64": 108660633.6,
+        "mixed": 108660633.6,
+        "separable": 108660633.6,
     },
 }
 TRAFFIC_SOURCES = ("paper_1805_11169_amd/csrc/k_matrices.hip", "paper_1805_11169_amd/csrc/icwf_device.hpp",
